@@ -165,6 +165,7 @@ struct Context {
     int64_t* bnd = nullptr; // 2 x (kMaxGrid + 1)
     unsigned long long* deg = nullptr;
     int64_t deg_cap = 0;
+    unsigned long long* tops = nullptr; // 4 x kMaxGrid: samples and largest count per row and column block
     // debug
     uint32_t* visits = nullptr;
     int64_t visits_cap = 0, visits_n = 0;
@@ -303,6 +304,7 @@ void release_all()
     dfree(c.totals);
     dfree(c.bnd);
     dfree(c.deg);
+    dfree(c.tops);
     dfree(c.hot.bits);
     dfree(c.maxdeg);
     dfree(c.visits);
@@ -738,7 +740,7 @@ int row_stats(const mfsgd_sample* samples, int64_t nnz, hipStream_t st)
     HIPCHK(hipMemsetAsync(c.bad, 0, sizeof(int), st));
     HIPCHK(hipMemsetAsync(c.deg, 0, sizeof(unsigned long long) * (size_t)(c.m + c.n), st));
     HIPCHK(hipMemsetAsync(c.maxdeg, 0, 2 * sizeof(unsigned long long), st));
-    HIPCHK(plan_degrees((const Sample*)samples, nnz, c.m, c.n, c.deg, c.deg + c.m, c.bad, st));
+    HIPCHK(plan_degrees((const Sample*)samples, nnz, nnz, c.m, c.n, c.deg, c.deg + c.m, c.bad, st));
     HIPCHK(max_degree(c.deg, c.m, c.maxdeg, st));
     HIPCHK(max_degree(c.deg + c.m, c.n, c.maxdeg + 1, st));
     unsigned long long h[2] = {0, 0};
@@ -768,7 +770,7 @@ int build_hot(const mfsgd_sample* samples, int64_t nnz, int log2, hipStream_t st
     CHK(grow(&c.deg, &c.deg_cap, c.m + c.n, "plan degrees"));
     HIPCHK(hipMemsetAsync(c.bad, 0, sizeof(int), st));
     HIPCHK(hipMemsetAsync(c.deg, 0, sizeof(unsigned long long) * (size_t)(c.m + c.n), st));
-    HIPCHK(plan_degrees((const Sample*)samples, nnz, c.m, c.n, c.deg, c.deg + c.m, c.bad, st));
+    HIPCHK(plan_degrees((const Sample*)samples, nnz, nnz, c.m, c.n, c.deg, c.deg + c.m, c.bad, st));
     const unsigned long long thr = std::max<unsigned long long>(1ull, (unsigned long long)nnz >> log2);
     HIPCHK(hot_bits(c.deg, c.m, thr, h.bits, st));
     HIPCHK(hot_bits(c.deg + c.m, c.n, thr, h.bits + wp, st));
@@ -784,16 +786,17 @@ int build_hot(const mfsgd_sample* samples, int64_t nnz, int log2, hipStream_t st
     return MFSGD_OK;
 }
 
+// Samples whose indices are counted for the hot-row and hot-column measures of
+// an equal-range plan: enough that each of 64 blocks holds about 16,000 of
+// them, a share known to 1 %.
+constexpr int64_t kPlanPicks = int64_t(1) << 20;
+
 int build_plan(Plan& pl, const mfsgd_sample* samples, int64_t nnz, int s, bool balanced, bool keep_orig,
                hipStream_t st)
 {
     Context& c = g;
     pl.invalidate();
-    // chunks: enough wavefronts to hide the scatter's latency on large sample arrays
-    int64_t chunks = (nnz + kPlanChunkSamples - 1) / kPlanChunkSamples;
-    chunks = std::min<int64_t>(std::max<int64_t>(chunks, kPlanChunksMin), kPlanChunksMax);
-    chunks = std::min<int64_t>(chunks, kPlanCountBytes / (int64_t)(sizeof(int64_t) * s * s));
-    chunks = std::max<int64_t>(256, chunks / 256 * 256);
+    const int chunks = kPlanChunks;
     CHK(grow(&c.counts, &c.counts_cap, (int64_t)s * s * chunks, "plan counts"));
     if (!c.totals)
         CHK(dalloc((void**)&c.totals, sizeof(int64_t) * kMaxGrid * kMaxGrid, "plan totals"));
@@ -804,54 +807,46 @@ int build_plan(Plan& pl, const mfsgd_sample* samples, int64_t nnz, int s, bool b
         CHK(grow(&pl.orig, &pl.orig_cap, nnz, "plan positions"));
     const Sample* S = (const Sample*)samples;
     HIPCHK(hipMemsetAsync(c.bad, 0, sizeof(int), st));
-    const int64_t* rbnd = nullptr;
-    const int64_t* cbnd = nullptr;
-    // per-index sample counts: the balanced cut and the hot-row and
-    // hot-column measures below need both
+    // Per-index sample counts.  The balanced cut needs all of them, exactly.
+    // The hot-row and hot-column measures only choose between two forms of
+    // the same update (skip_stores), so for equal ranges they come from
+    // kPlanPicks samples spread over the array: on 384 M samples the counts of
+    // all of them took 31.5 ms (bound by one memory-side atomic per distinct
+    // user of a tile), the copy of the counts to the host and the loops over
+    // them there as long again, against 0.2 ms.
     CHK(grow(&c.deg, &c.deg_cap, c.m + c.n, "plan degrees"));
+    if (!c.tops)
+        CHK(dalloc((void**)&c.tops, sizeof(unsigned long long) * 4 * kMaxGrid, "block tops"));
     HIPCHK(hipMemsetAsync(c.deg, 0, sizeof(unsigned long long) * (size_t)(c.m + c.n), st));
-    HIPCHK(plan_degrees(S, nnz, c.m, c.n, c.deg, c.deg + c.m, c.bad, st));
-    std::vector<unsigned long long> du((size_t)c.m), dv((size_t)c.n);
-    HIPCHK(hipMemcpyAsync(du.data(), c.deg, sizeof(unsigned long long) * du.size(), hipMemcpyDeviceToHost, st));
-    HIPCHK(hipMemcpyAsync(dv.data(), c.deg + c.m, sizeof(unsigned long long) * dv.size(), hipMemcpyDeviceToHost, st));
-    HIPCHK(hipMemcpyAsync(c.hflag, c.bad, sizeof(int), hipMemcpyDeviceToHost, st));
-    HIPCHK(hipStreamSynchronize(st));
-    if (*c.hflag) {
-        *c.hflag = 0;
-        return bad_index_error();
-    }
+    HIPCHK(plan_degrees(S, nnz, balanced ? nnz : std::min(nnz, kPlanPicks), c.m, c.n, c.deg, c.deg + c.m, c.bad, st));
     std::vector<int64_t> cut(2 * (kMaxGrid + 1));
     int64_t* ccut = cut.data() + kMaxGrid + 1;
     if (balanced) {
+        std::vector<unsigned long long> du((size_t)c.m), dv((size_t)c.n);
+        HIPCHK(hipMemcpyAsync(du.data(), c.deg, sizeof(unsigned long long) * du.size(), hipMemcpyDeviceToHost, st));
+        HIPCHK(
+            hipMemcpyAsync(dv.data(), c.deg + c.m, sizeof(unsigned long long) * dv.size(), hipMemcpyDeviceToHost, st));
+        HIPCHK(hipMemcpyAsync(c.hflag, c.bad, sizeof(int), hipMemcpyDeviceToHost, st));
+        HIPCHK(hipStreamSynchronize(st));
+        if (*c.hflag) {
+            *c.hflag = 0;
+            return bad_index_error();
+        }
         balanced_cut(du, nnz, s, cut.data());
         balanced_cut(dv, nnz, s, ccut);
-        HIPCHK(hipMemcpy(c.bnd, cut.data(), sizeof(int64_t) * cut.size(), hipMemcpyHostToDevice));
-        rbnd = c.bnd;
-        cbnd = c.bnd + kMaxGrid + 1;
     } else {
         for (int j = 0; j <= s; ++j) { // first index of each equal range floor(x*s/N) = j
             cut[j] = (int64_t)((j * c.m + s - 1) / s);
             ccut[j] = (int64_t)((j * c.n + s - 1) / s);
         }
     }
-    // Largest share of one block row's (column's) samples that a single user
-    // (item) holds.
-    auto hottest = [s](const std::vector<unsigned long long>& d, const int64_t* bnd) {
-        double h = 0.0;
-        for (int j = 0; j < s; ++j) {
-            unsigned long long tot = 0, top = 0;
-            for (int64_t x = bnd[j]; x < bnd[j + 1]; ++x) {
-                tot += d[(size_t)x];
-                top = std::max(top, d[(size_t)x]);
-            }
-            if (tot > 0)
-                h = std::max(h, (double)top / (double)tot);
-        }
-        return h;
-    };
-    pl.hot_row = hottest(du, cut.data());
-    pl.hot_col = hottest(dv, ccut);
-    PlanBuffers b{c.counts, (int)chunks, c.totals, pl.bstart, pl.Sp, keep_orig ? pl.orig : nullptr, c.bad, rbnd, cbnd};
+    HIPCHK(hipMemcpyAsync(c.bnd, cut.data(), sizeof(int64_t) * cut.size(), hipMemcpyHostToDevice, st));
+    // samples and largest count of every row block, then of every column block
+    std::vector<unsigned long long> tops(4 * (size_t)s);
+    HIPCHK(block_tops(c.deg, c.deg + c.m, c.bnd, c.bnd + kMaxGrid + 1, s, c.tops, st));
+    HIPCHK(hipMemcpyAsync(tops.data(), c.tops, sizeof(unsigned long long) * tops.size(), hipMemcpyDeviceToHost, st));
+    PlanBuffers b{c.counts, chunks, c.totals, pl.bstart, pl.Sp, keep_orig ? pl.orig : nullptr, c.bad,
+                  c.bnd,    c.bnd + kMaxGrid + 1, !balanced};
     HIPCHK(plan_build(S, nnz, c.m, c.n, s, b, st));
     HIPCHK(hipMemcpyAsync(c.hflag, c.bad, sizeof(int), hipMemcpyDeviceToHost, st));
     HIPCHK(hipStreamSynchronize(st));
@@ -859,6 +854,14 @@ int build_plan(Plan& pl, const mfsgd_sample* samples, int64_t nnz, int s, bool b
     *c.hflag = 0;
     if (bad)
         return bad_index_error();
+    // largest share of one row block's (column block's) samples that a single
+    // user (item) holds
+    pl.hot_row = pl.hot_col = 0.0;
+    for (int j = 0; j < 2 * s; ++j)
+        if (tops[2 * (size_t)j] > 0) {
+            double& h = j < s ? pl.hot_row : pl.hot_col;
+            h = std::max(h, (double)tops[2 * (size_t)j + 1] / (double)tops[2 * (size_t)j]);
+        }
     HIPCHK(plan_scatter(S, nnz, c.m, c.n, s, b, st));
     pl.hstart.assign((size_t)s * s + 1, 0);
     HIPCHK(hipMemcpyAsync(pl.hstart.data(), pl.bstart, sizeof(int64_t) * pl.hstart.size(), hipMemcpyDeviceToHost,

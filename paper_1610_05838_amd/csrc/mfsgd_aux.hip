@@ -136,36 +136,43 @@ hipError_t probe_xcc(int* out, int n, hipStream_t st)
 // ---------------------------------------------------------------------------
 // Planner: a stable counting sort of the samples by block id
 // (row block floor(u*s/m)) * s + (column block floor(v*s/n)).
-//   1. each of kPlanChunks wavefronts counts its contiguous chunk per block
-//      (and flags indices out of range);
+//   1. each of `chunks` workgroups counts its contiguous chunk per block (and
+//      flags indices out of range);
 //   2. per block, an exclusive scan over the chunks;
 //   3. an exclusive scan over the blocks gives the block starts;
-//   4. each wavefront walks its chunk in order, 64 samples at a time, ranks
-//      equal blocks by lane (ballot peeling) and scatters the samples.
+//   4. one wavefront per chunk walks it in order, 64 samples at a time, ranks
+//      the samples of equal blocks by lane and scatters them.
 // Chunks, steps and lanes are all taken in array order, so every block keeps
 // its samples in array order.
 // ---------------------------------------------------------------------------
-// Block cut: equal index ranges (floor(i*s/N)) when no bounds are given,
-// else the consecutive ranges bounds[0..s] (index i is in the last range
-// whose first index is <= i).
+// Block cut: the first index of every range, rb[0..s] and cb[0..s] (rb[s] = m,
+// cb[s] = n; index i is in the last range whose first index is <= i), and for
+// equal index ranges (floor(i*s/N)) the scale s/N (0: ranges of other sizes).
 struct Cut {
-    int64_t rb[kMaxGrid + 1];
-    int64_t cb[kMaxGrid + 1];
-    bool bounded;
+    int rb[kMaxGrid + 1];
+    int cb[kMaxGrid + 1];
 };
 
-__device__ __forceinline__ void load_cut(Cut& c, const int64_t* rbnd, const int64_t* cbnd, int s)
+__device__ __forceinline__ void load_cut(Cut& c, const int64_t* __restrict__ rbnd, const int64_t* __restrict__ cbnd,
+                                         int s)
 {
-    c.bounded = rbnd != nullptr;
-    if (c.bounded)
-        for (int i = threadIdx.x; i <= s; i += blockDim.x) {
-            c.rb[i] = rbnd[i];
-            c.cb[i] = cbnd[i];
-        }
+    for (int i = threadIdx.x; i <= s; i += blockDim.x) {
+        c.rb[i] = (int)rbnd[i];
+        c.cb[i] = (int)cbnd[i];
+    }
 }
 
-__device__ __forceinline__ int range_of(int64_t i, const int64_t* b, int s)
+// The range of index i.  Equal ranges: i * (s/N) in binary32 is off by less
+// than one range (i, s and N are each rounded once, s <= 64), so one look at
+// the guessed range's two ends settles it; the 64-bit division this replaces
+// took most of the counting kernel's instructions.  Other cuts: bisection.
+__device__ __forceinline__ int range_of(int i, const int* b, int s, float scale)
 {
+    if (scale > 0.f) {
+        int q = (int)((float)i * scale);
+        q = q < s ? q : s - 1;
+        return q - (i < b[q] ? 1 : 0) + (i >= b[q + 1] ? 1 : 0);
+    }
     int lo = 0, hi = s - 1; // largest k in [0, s-1] with b[k] <= i
     while (lo < hi) {
         const int mid = (lo + hi + 1) >> 1;
@@ -177,13 +184,9 @@ __device__ __forceinline__ int range_of(int64_t i, const int64_t* b, int s)
     return lo;
 }
 
-__device__ __forceinline__ int block_of(int u, int v, int64_t m, int64_t n, int s, const Cut& c)
+__device__ __forceinline__ int block_of(int u, int v, int s, float su, float sv, const Cut& c)
 {
-    if (c.bounded)
-        return range_of(u, c.rb, s) * s + range_of(v, c.cb, s);
-    const int rb = (int)(((int64_t)u * s) / m);
-    const int cb = (int)(((int64_t)v * s) / n);
-    return rb * s + cb;
+    return range_of(u, c.rb, s, su) * s + range_of(v, c.cb, s, sv);
 }
 
 // Per-index sample counts (users and items) for the balanced cut and the
@@ -210,8 +213,19 @@ __device__ __forceinline__ void deg_insert(int* keys, unsigned* cnt, int key)
     }
 }
 
-__global__ __launch_bounds__(256) void k_degrees(const Sample* __restrict__ S, int64_t nnz, int64_t m, int64_t n,
-                                                 unsigned long long* __restrict__ du,
+// One position of each of `picks` equal cells of the array, at a place of its
+// own inside the cell (hashed, so no regular order of the array can hide an
+// index from the picks); every position when picks == nnz.
+__device__ __forceinline__ int64_t pick_position(int64_t i, int64_t picks, int64_t nnz)
+{
+    if (picks == nnz)
+        return i;
+    const int64_t lo = i * nnz / picks, hi = (i + 1) * nnz / picks; // picks <= 2^20 here: no overflow
+    return lo + (int64_t)(((sm64_at(0, (uint64_t)i) >> 32) * (uint64_t)(hi - lo)) >> 32);
+}
+
+__global__ __launch_bounds__(256) void k_degrees(const Sample* __restrict__ S, int64_t nnz, int64_t picks, int64_t m,
+                                                 int64_t n, unsigned long long* __restrict__ du,
                                                  unsigned long long* __restrict__ dv, int* bad)
 {
     __shared__ int ku[kDegSlots], kv[kDegSlots];
@@ -222,13 +236,14 @@ __global__ __launch_bounds__(256) void k_degrees(const Sample* __restrict__ S, i
     }
     __syncthreads();
     int found = 0;
-    const int64_t tiles = (nnz + kDegTile - 1) / kDegTile;
+    const int64_t tiles = (picks + kDegTile - 1) / kDegTile;
     for (int64_t t = blockIdx.x; t < tiles; t += gridDim.x) {
         const int64_t lo = t * kDegTile;
-        const int64_t hi = lo + kDegTile < nnz ? lo + kDegTile : nnz;
+        const int64_t hi = lo + kDegTile < picks ? lo + kDegTile : picks;
         for (int64_t i = lo + threadIdx.x; i < hi; i += blockDim.x) {
-            const int u = __builtin_nontemporal_load(&S[i].u);
-            const int v = __builtin_nontemporal_load(&S[i].v);
+            const Sample* x = S + pick_position(i, picks, nnz);
+            const int u = __builtin_nontemporal_load(&x->u);
+            const int v = __builtin_nontemporal_load(&x->v);
             if (u < 0 || u >= m || v < 0 || v >= n) {
                 found = 1;
                 continue;
@@ -253,6 +268,52 @@ __global__ __launch_bounds__(256) void k_degrees(const Sample* __restrict__ S, i
     }
     if (found)
         atomicOr(bad, 1);
+}
+
+// Samples of every row block and column block, and the most any one index of
+// it holds: workgroup j < s takes row block j (users bnd[j] .. bnd[j+1]-1),
+// workgroup s + j column block j; out[2 j] = samples, out[2 j + 1] = largest.
+__global__ __launch_bounds__(1024) void k_block_tops(const unsigned long long* __restrict__ du,
+                                                     const unsigned long long* __restrict__ dv,
+                                                     const int64_t* __restrict__ rbnd, const int64_t* __restrict__ cbnd,
+                                                     int s, unsigned long long* __restrict__ out)
+{
+    const bool col = (int)blockIdx.x >= s;
+    const int j = col ? (int)blockIdx.x - s : (int)blockIdx.x;
+    const unsigned long long* d = col ? dv : du;
+    const int64_t* bnd = col ? cbnd : rbnd;
+    unsigned long long sum = 0, top = 0;
+    for (int64_t i = bnd[j] + threadIdx.x; i < bnd[j + 1]; i += blockDim.x) {
+        const unsigned long long x = d[i];
+        sum += x;
+        top = x > top ? x : top;
+    }
+    for (int o = 32; o > 0; o >>= 1) {
+        sum += __shfl_xor(sum, o);
+        const unsigned long long y = __shfl_xor(top, o);
+        top = y > top ? y : top;
+    }
+    __shared__ unsigned long long ws[16], wt[16];
+    if ((threadIdx.x & 63) == 0) {
+        ws[threadIdx.x >> 6] = sum;
+        wt[threadIdx.x >> 6] = top;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int w = 1; w < 16; ++w) {
+            sum += ws[w];
+            top = wt[w] > top ? wt[w] : top;
+        }
+        out[2 * blockIdx.x] = sum;
+        out[2 * blockIdx.x + 1] = top;
+    }
+}
+
+hipError_t block_tops(const unsigned long long* du, const unsigned long long* dv, const int64_t* rbnd,
+                      const int64_t* cbnd, int s, unsigned long long* out, hipStream_t st)
+{
+    hipLaunchKernelGGL(k_block_tops, dim3(2 * s), dim3(1024), 0, st, du, dv, rbnd, cbnd, s, out);
+    return hipGetLastError();
 }
 
 // One thread per 32 rows: no atomics, every word written once.
@@ -310,26 +371,32 @@ hipError_t max_degree(const unsigned long long* deg, int64_t rows, unsigned long
     return hipGetLastError();
 }
 
-hipError_t plan_degrees(const Sample* S, int64_t nnz, int64_t m, int64_t n, unsigned long long* du,
+hipError_t plan_degrees(const Sample* S, int64_t nnz, int64_t picks, int64_t m, int64_t n, unsigned long long* du,
                         unsigned long long* dv, int* bad, hipStream_t st)
 {
     if (nnz <= 0)
         return hipSuccess;
-    int64_t blocks = (nnz + kDegTile - 1) / kDegTile;
+    if (picks > nnz)
+        picks = nnz;
+    int64_t blocks = (picks + kDegTile - 1) / kDegTile;
     if (blocks > 2048)
         blocks = 2048;
-    hipLaunchKernelGGL(k_degrees, dim3((unsigned)blocks), dim3(256), 0, st, S, nnz, m, n, du, dv, bad);
+    hipLaunchKernelGGL(k_degrees, dim3((unsigned)blocks), dim3(256), 0, st, S, nnz, picks, m, n, du, dv, bad);
     return hipGetLastError();
 }
 
-__global__ __launch_bounds__(64) void k_plan_count(const Sample* __restrict__ S, int64_t nnz, int64_t m, int64_t n,
-                                                   int s, const int64_t* rbnd, const int64_t* cbnd,
-                                                   int64_t* __restrict__ counts, int chunks, int* bad)
+// Sixteen wavefronts share a chunk's histogram (up to 16 KB of LDS), two
+// workgroups fill a CU; bound by reading the samples (384 M: 3.84 ms with one
+// wavefront per workgroup and 64-bit divisions, 0.78 ms so, 5.9 TB/s).
+__global__ __launch_bounds__(1024) void k_plan_count(const Sample* __restrict__ S, int64_t nnz, int m, int n, int s,
+                                                    float su, float sv, const int64_t* __restrict__ rbnd,
+                                                    const int64_t* __restrict__ cbnd, int64_t* __restrict__ counts,
+                                                    int chunks, int* bad)
 {
-    __shared__ int hist[kMaxGrid * kMaxGrid];
     __shared__ Cut cut;
+    extern __shared__ int hist[]; // s*s
     const int nb = s * s;
-    for (int i = threadIdx.x; i < nb; i += 64)
+    for (int i = threadIdx.x; i < nb; i += blockDim.x)
         hist[i] = 0;
     load_cut(cut, rbnd, cbnd, s);
     __syncthreads();
@@ -337,19 +404,32 @@ __global__ __launch_bounds__(64) void k_plan_count(const Sample* __restrict__ S,
     const int64_t lo = (int64_t)blockIdx.x * cs;
     const int64_t hi = lo + cs < nnz ? lo + cs : nnz;
     int found = 0;
-    for (int64_t i = lo + threadIdx.x; i < hi; i += 64) {
-        const int u = __builtin_nontemporal_load(&S[i].u);
-        const int v = __builtin_nontemporal_load(&S[i].v);
-        if (u < 0 || u >= m || v < 0 || v >= n) {
-            found = 1;
-            continue;
+    for (int64_t i0 = lo + threadIdx.x; i0 < hi; i0 += 4 * (int64_t)blockDim.x) {
+        int u[4], v[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int64_t i = i0 + r * (int64_t)blockDim.x;
+            u[r] = v[r] = 0;
+            if (i < hi) {
+                u[r] = __builtin_nontemporal_load(&S[i].u);
+                v[r] = __builtin_nontemporal_load(&S[i].v);
+            }
         }
-        atomicAdd(&hist[block_of(u, v, m, n, s, cut)], 1);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            if (i0 + r * (int64_t)blockDim.x >= hi)
+                break;
+            if ((unsigned)u[r] >= (unsigned)m || (unsigned)v[r] >= (unsigned)n) {
+                found = 1;
+                continue;
+            }
+            atomicAdd(&hist[block_of(u[r], v[r], s, su, sv, cut)], 1);
+        }
     }
     if (found)
         atomicOr(bad, 1);
     __syncthreads();
-    for (int b = threadIdx.x; b < nb; b += 64)
+    for (int b = threadIdx.x; b < nb; b += blockDim.x)
         counts[(int64_t)b * chunks + blockIdx.x] = hist[b];
 }
 
@@ -417,59 +497,127 @@ __global__ __launch_bounds__(1024) void k_plan_scan_blocks(const int64_t* __rest
         bstart[nb] = part[1023];
 }
 
-__global__ __launch_bounds__(64) void k_plan_scatter(const Sample* __restrict__ S, int64_t nnz, int64_t m, int64_t n,
-                                                     int s, const int64_t* rbnd, const int64_t* cbnd,
-                                                     const int64_t* __restrict__ counts, int chunks,
-                                                     const int64_t* __restrict__ bstart, Sample* __restrict__ Sp,
-                                                     int64_t* __restrict__ orig)
+// One workgroup of NW wavefronts per chunk, in tiles of NW * kPlanRounds * 64
+// samples, wavefront w taking the w-th part of the tile.
+//   * Within 64 samples the ones of one block find each other with one ballot
+//     per bit of the block id (BITS bits): a lane keeps the lanes that agree
+//     with it on every bit; its rank is the number of those below it plus the
+//     wavefront's count of the block so far, which the first of them moves on.
+//     A fixed number of instructions, where taking a step's distinct blocks
+//     one after the other needs up to 64 rounds.
+//   * Per tile the wavefronts' counts are turned into prefix sums, block by
+//     block, which puts the wavefronts' parts in array order.
+// What bounds it is the scattered 12-byte write: at s = 64 a chunk has 4096
+// lines open, and only lines that stay in the 256 MB Infinity Cache until the
+// chunk has filled them reach memory once.  One chunk per CU at a time (256
+// x 4096 lines of 128 B = 134 MB) does that.  384 M samples at s = 64: 51.8 ms
+// taking the distinct blocks one by one, 14.1 ms with the ballots and a chunk
+// per wavefront (2560 chunks in flight, most lines written several times
+// over), 6.2 ms so; 99 M samples at s = 32: 11.9 ms to 1.1 ms.
+// OFF: the positions' type, 32 bits where nnz fits them.
+constexpr int kPlanRounds = 8;
+
+template <int BITS, typename OFF, int NW>
+__global__ __launch_bounds__(64 * NW) void k_plan_scatter(const Sample* __restrict__ S, int64_t nnz, int m, int n,
+                                                          int s, float su, float sv,
+                                                          const int64_t* __restrict__ rbnd,
+                                                          const int64_t* __restrict__ cbnd,
+                                                          const int64_t* __restrict__ counts, int chunks,
+                                                          const int64_t* __restrict__ bstart,
+                                                          Sample* __restrict__ Sp, int64_t* __restrict__ orig)
 {
-    __shared__ int64_t base[kMaxGrid * kMaxGrid];
+    constexpr int kBins = 1 << BITS;
+    constexpr int kThreads = 64 * NW;
+    constexpr int kPer = (kBins + kThreads - 1) / kThreads; // bins per thread
+    __shared__ OFF base[kBins];
+    __shared__ __align__(16) uint16_t cnt[NW][kBins]; // at most 64 * kPlanRounds per wavefront and tile
     __shared__ Cut cut;
     const int nb = s * s;
-    for (int b = threadIdx.x; b < nb; b += 64)
-        base[b] = bstart[b] + counts[(int64_t)b * chunks + blockIdx.x];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    for (int b = threadIdx.x; b < nb; b += kThreads)
+        base[b] = (OFF)(bstart[b] + counts[(int64_t)b * chunks + blockIdx.x]);
     load_cut(cut, rbnd, cbnd, s);
-    __syncthreads();
-    const int lane = threadIdx.x;
-    const uint64_t below = (lane == 0) ? 0ull : ((~0ull) >> (64 - lane));
     const int64_t cs = (nnz + chunks - 1) / chunks;
     const int64_t lo = (int64_t)blockIdx.x * cs;
     const int64_t hi = lo + cs < nnz ? lo + cs : nnz;
-    for (int64_t c0 = lo; c0 < hi; c0 += 64) {
-        const int64_t i = c0 + lane;
-        bool valid = i < hi;
-        Sample x{0, 0, 0.f};
-        int b = -1;
-        if (valid) {
-            x.u = __builtin_nontemporal_load(&S[i].u);
-            x.v = __builtin_nontemporal_load(&S[i].v);
-            x.r = __builtin_nontemporal_load(&S[i].r);
-            valid = x.u >= 0 && x.u < m && x.v >= 0 && x.v < n; // the host never scatters a plan with bad indices
-            if (valid)
-                b = block_of(x.u, x.v, m, n, s, cut);
+    for (int64_t t0 = lo; t0 < hi; t0 += (int64_t)kThreads * kPlanRounds) {
+        Sample x[kPlanRounds];
+        int at[kPlanRounds], bin[kPlanRounds];
+        const int64_t i0 = t0 + (int64_t)w * (64 * kPlanRounds) + lane;
+#pragma unroll
+        for (int r = 0; r < kPlanRounds; ++r) {
+            x[r] = Sample{-1, -1, 0.f};
+            if (i0 + 64 * r < hi) {
+                x[r].u = __builtin_nontemporal_load(&S[i0 + 64 * r].u);
+                x[r].v = __builtin_nontemporal_load(&S[i0 + 64 * r].v);
+                x[r].r = __builtin_nontemporal_load(&S[i0 + 64 * r].r);
+            }
         }
-        uint64_t pending = __ballot(valid);
-        int64_t dest = -1;
-        while (pending) {
-            const int leader = __ffsll((unsigned long long)pending) - 1;
-            const int lb = __builtin_amdgcn_readlane(b, leader);
-            const uint64_t same = __ballot(b == lb) & pending;
-            const int64_t at = base[lb];
-            if ((same >> lane) & 1ull)
-                dest = at + __popcll(same & below);
-            __syncthreads();
-            if (lane == leader)
-                base[lb] = at + __popcll(same);
-            __syncthreads();
-            pending &= ~same;
+        for (int j = threadIdx.x; j < NW * kBins / 8; j += kThreads)
+            reinterpret_cast<uint4*>(&cnt[0][0])[j] = uint4{0u, 0u, 0u, 0u};
+        __syncthreads(); // counts cleared; base and cut in place
+#pragma unroll
+        for (int r = 0; r < kPlanRounds; ++r) {
+            // the host never scatters a plan with bad indices; a lane past the
+            // chunk's end holds -1
+            const bool valid = (unsigned)x[r].u < (unsigned)m && (unsigned)x[r].v < (unsigned)n;
+            const int b = valid ? block_of(x[r].u, x[r].v, s, su, sv, cut) : 0;
+            const uint64_t same = __ballot(valid);
+            uint32_t lo32 = (uint32_t)same, hi32 = (uint32_t)(same >> 32);
+#pragma unroll
+            for (int k = 0; k < BITS; ++k) {
+                const bool one = ((b >> k) & 1) != 0;
+                const uint64_t ones = __ballot(one);
+                const uint32_t flip = one ? 0u : ~0u;
+                lo32 &= (uint32_t)ones ^ flip;
+                hi32 &= (uint32_t)(ones >> 32) ^ flip;
+            }
+            const int rank = (int)__builtin_amdgcn_mbcnt_hi(hi32, __builtin_amdgcn_mbcnt_lo(lo32, 0u));
+            bin[r] = valid ? b : -1;
+            at[r] = 0;
+            if (valid) {
+                const int have = cnt[w][b];
+                at[r] = have + rank;
+                if (rank == 0) // after every lane's read: a wavefront's LDS accesses complete in order
+                    cnt[w][b] = (uint16_t)(have + __popc(lo32) + __popc(hi32));
+            }
         }
-        if (valid) {
-            Sp[dest] = x;
-            if (orig)
-                orig[dest] = i;
+        __syncthreads();
+        uint32_t total[kPer];
+#pragma unroll
+        for (int p = 0; p < kPer; ++p) {
+            const int b = threadIdx.x + p * kThreads;
+            uint32_t run = 0;
+            if (b < kBins) {
+#pragma unroll
+                for (int v = 0; v < NW; ++v) {
+                    const uint32_t c = cnt[v][b];
+                    cnt[v][b] = (uint16_t)run;
+                    run += c;
+                }
+            }
+            total[p] = run;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < kPlanRounds; ++r)
+            if (bin[r] >= 0) {
+                const int64_t dest = (int64_t)base[bin[r]] + cnt[w][bin[r]] + at[r];
+                Sp[dest] = x[r];
+                if (orig)
+                    orig[dest] = i0 + 64 * r;
+            }
+        __syncthreads(); // every position read before the blocks' bases move on
+#pragma unroll
+        for (int p = 0; p < kPer; ++p) {
+            const int b = threadIdx.x + p * kThreads;
+            if (b < kBins)
+                base[b] += (OFF)total[p];
         }
     }
 }
+
+static float cut_scale(int64_t N, int s, bool equal) { return equal ? (float)s / (float)N : 0.f; }
 
 hipError_t plan_build(const Sample* S, int64_t nnz, int64_t m, int64_t n, int s, const PlanBuffers& b,
                       hipStream_t st)
@@ -477,18 +625,40 @@ hipError_t plan_build(const Sample* S, int64_t nnz, int64_t m, int64_t n, int s,
     const int nb = s * s;
     if (b.chunks < 256 || b.chunks % 256 != 0)
         return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_plan_count, dim3(b.chunks), dim3(64), 0, st, S, nnz, m, n, s, b.rbnd, b.cbnd, b.counts,
-                       b.chunks, b.bad);
+    hipLaunchKernelGGL(k_plan_count, dim3(b.chunks), dim3(1024), sizeof(int) * (size_t)nb, st, S, nnz, (int)m, (int)n,
+                       s, cut_scale(m, s, b.equal), cut_scale(n, s, b.equal), b.rbnd, b.cbnd, b.counts, b.chunks,
+                       b.bad);
     hipLaunchKernelGGL(k_plan_scan_chunks, dim3(nb), dim3(256), 0, st, b.counts, b.chunks, b.totals);
     hipLaunchKernelGGL(k_plan_scan_blocks, dim3(1), dim3(1024), 0, st, b.totals, nb, b.bstart);
     return hipGetLastError();
 }
 
+template <int BITS>
+static void launch_scatter(const Sample* S, int64_t nnz, int64_t m, int64_t n, int s, const PlanBuffers& b,
+                           hipStream_t st)
+{
+    const float su = cut_scale(m, s, b.equal), sv = cut_scale(n, s, b.equal);
+    if (nnz <= 0xffffffffll)
+        hipLaunchKernelGGL((k_plan_scatter<BITS, uint32_t, 16>), dim3(b.chunks), dim3(1024), 0, st, S, nnz, (int)m, (int)n,
+                           s, su, sv, b.rbnd, b.cbnd, b.counts, b.chunks, b.bstart, b.Sp, b.orig);
+    else
+        hipLaunchKernelGGL((k_plan_scatter<BITS, uint64_t, 8>), dim3(b.chunks), dim3(512), 0, st, S, nnz, (int)m, (int)n,
+                           s, su, sv, b.rbnd, b.cbnd, b.counts, b.chunks, b.bstart, b.Sp, b.orig);
+}
+
 hipError_t plan_scatter(const Sample* S, int64_t nnz, int64_t m, int64_t n, int s, const PlanBuffers& b,
                         hipStream_t st)
 {
-    hipLaunchKernelGGL(k_plan_scatter, dim3(b.chunks), dim3(64), 0, st, S, nnz, m, n, s, b.rbnd, b.cbnd,
-                       b.counts, b.chunks, b.bstart, b.Sp, b.orig);
+    if (s <= 4)
+        launch_scatter<4>(S, nnz, m, n, s, b, st);
+    else if (s <= 8)
+        launch_scatter<6>(S, nnz, m, n, s, b, st);
+    else if (s <= 16)
+        launch_scatter<8>(S, nnz, m, n, s, b, st);
+    else if (s <= 32)
+        launch_scatter<10>(S, nnz, m, n, s, b, st);
+    else
+        launch_scatter<12>(S, nnz, m, n, s, b, st);
     return hipGetLastError();
 }
 

@@ -134,23 +134,25 @@ struct PlanBuffers {
     Sample* Sp;          // planned copy
     int64_t* orig;       // planned position -> caller position (optional)
     int* bad;            // index-range flag
-    const int64_t* rbnd; // balanced cut (s+1 user bounds), or nullptr for equal ranges
-    const int64_t* cbnd; // s+1 item bounds
+    const int64_t* rbnd; // first user of every row block, then m (s+1 entries)
+    const int64_t* cbnd; // first item of every column block, then n
+    bool equal;          // equal index ranges (floor(i*s/N)) rather than another cut
 };
-// per-index sample counts for the balanced cut (indices out of range raise *bad)
-hipError_t plan_degrees(const Sample* S, int64_t nnz, int64_t m, int64_t n, unsigned long long* du,
+// per-index sample counts (indices out of range raise *bad) of all samples, or
+// of `picks` < nnz of them spread evenly over the array
+hipError_t plan_degrees(const Sample* S, int64_t nnz, int64_t picks, int64_t m, int64_t n, unsigned long long* du,
                         unsigned long long* dv, int* bad, hipStream_t st);
+// out[2 j], out[2 j + 1] = samples and largest count of one index, for the s
+// row blocks (users rbnd[j] .. rbnd[j+1]-1), then the s column blocks
+hipError_t block_tops(const unsigned long long* du, const unsigned long long* dv, const int64_t* rbnd,
+                      const int64_t* cbnd, int s, unsigned long long* out, hipStream_t st);
 // *out = max(*out, deg[0 .. rows-1]) (the caller zeroes *out first)
 hipError_t max_degree(const unsigned long long* deg, int64_t rows, unsigned long long* out, hipStream_t st);
 // bits[i / 32] bit i % 32 = (deg[i] >= thr), for rows 0 .. rows-1 (the last word's spare bits clear)
 hipError_t hot_bits(const unsigned long long* deg, int64_t rows, unsigned long long thr, uint32_t* bits,
                     hipStream_t st);
-// chunks of a plan: about one per kPlanChunkSamples samples, between
-// kPlanChunksMin and kPlanChunksMax, and at most kPlanCountBytes of counts
-constexpr int kPlanChunksMin = 2048;
-constexpr int kPlanChunksMax = 16384;
-constexpr int64_t kPlanChunkSamples = 65536;
-constexpr int64_t kPlanCountBytes = int64_t(512) << 20;
+// chunks of a plan: two workgroups' worth per CU of the scatter (one at a time at s > 32)
+constexpr int kPlanChunks = 512;
 // counts, per-block scans and block starts; raises *b.bad on an index out of range
 hipError_t plan_build(const Sample* S, int64_t nnz, int64_t m, int64_t n, int s, const PlanBuffers& b,
                       hipStream_t st);

@@ -1,0 +1,55 @@
+"""The wavefront-update planner against the oracle's stable bucketing: block
+starts and planned positions, bit for bit, at the grid sides where the
+scatter's block-id width changes (4, 8, 16, 32), at sizes around its tiles of
+8192 samples, for both cuts, and for models narrower than the grid."""
+import numpy as np
+import pytest
+
+import oracle
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def M():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1610_05838_amd import mfsgd
+    mfsgd.lib()
+    yield mfsgd
+    mfsgd.finalize()
+
+
+def samples(m, n, nnz, seed, skew):
+    rng = np.random.default_rng(seed)
+    S = np.zeros(nnz, dtype=[("u", "<i4"), ("v", "<i4"), ("r", "<f4")])
+    S["u"], S["v"], S["r"] = rng.integers(0, m, nnz), rng.integers(0, n, nnz), rng.random(nnz)
+    if skew and nnz:  # half of the samples on one item: equal blocks within one step of 64
+        S["v"][::2] = n - 1
+    return S
+
+
+@pytest.mark.parametrize("balance", [0, 1])
+@pytest.mark.parametrize("s", [1, 3, 4, 5, 8, 9, 16, 17, 32, 33, 64])
+def test_plan_equals_the_oracles_bucketing(M, s, balance):
+    M.reset_options()
+    M.set_option("balance", balance)
+    M.set_option("debug", 1)
+    for m, n, nnz in ((4001, 1999, 600_011), (4001, 1999, 8193), (3, 2, 8192), (200_000_033, 7, 1000), (77, 50, 63),
+                      (5, 70, 1), (5, 70, 0)):
+        if m > 1_000_000 and balance:
+            continue  # the balanced cut counts every index
+        M.set_option("dtype", 1)
+        M.init(m, n, 8, 1)
+        S = samples(m, n, nnz, 100 * s + nnz % 97, skew=nnz == 8193)
+        if m > 1_000_000:  # indices beyond 24 bits, at both ends of every range
+            edges = (np.arange(s + 1, dtype=np.int64) * m + s - 1) // s
+            ends = np.concatenate([edges[:-1], edges[1:] - 1]).astype(np.int32)
+            S["u"][:len(ends)] = ends
+        order, start = oracle.block_order(S, m, n, s, balanced=bool(balance))
+        dS = M.samples_to_device(S)
+        M.plan(dS, s)
+        got = M.debug_plan_starts(s).cpu().numpy()
+        assert np.array_equal(got, start), (m, n, nnz)
+        assert np.array_equal(M.debug_plan_order(nnz).cpu().numpy(), order), (m, n, nnz)
