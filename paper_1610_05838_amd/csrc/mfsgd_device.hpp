@@ -458,7 +458,8 @@ template <int KP, typename T, int D, bool DBG, bool SKIP = false, bool BUF = fal
 __device__ __forceinline__ void run_worker(const Sample* __restrict__ S, int64_t nnz, int64_t W, int64_t worker,
                                            int f, T* __restrict__ P, T* __restrict__ Q, float lr, float lp,
                                            float lq, const DebugSink dbg, const CacheSync sync = CacheSync{0, false, false},
-                                           T* sink = nullptr, const Coherence coh = Coherence{nullptr, nullptr, false, false})
+                                           T* sink = nullptr, const Coherence coh = Coherence{nullptr, nullptr, false, false},
+                                           uint32_t last_u = ~0u, uint32_t last_v = ~0u)
 {
     constexpr int E = Geo<KP>::E;
     static_assert(!BUF || (!SKIP && sizeof(T) * E == 4), "buffer rows: one dword per lane, no store redirection");
@@ -493,8 +494,8 @@ __device__ __forceinline__ void run_worker(const Sample* __restrict__ S, int64_t
         cnt = rem <= 0 ? 0 : (rem >= 64 ? 64 : (int)rem);
         const int64_t i = s0 + (lane < cnt ? lane : 0);
         const Sample* sp = S + (cnt > 0 ? i : 0);
-        cu = __builtin_nontemporal_load(&sp->u);
-        cv = __builtin_nontemporal_load(&sp->v);
+        cu = (int)min((uint32_t)__builtin_nontemporal_load(&sp->u), last_u);
+        cv = (int)min((uint32_t)__builtin_nontemporal_load(&sp->v), last_v);
         cr = __builtin_nontemporal_load(&sp->r);
     };
 
@@ -811,7 +812,8 @@ __device__ __forceinline__ void run_worker_half(const Sample* __restrict__ S, in
                                                 int f, T* __restrict__ P, T* __restrict__ Q, float lr, float lp,
                                                 float lq, const DebugSink dbg,
                                                 const CacheSync sync = CacheSync{0, false, false},
-                                                T* __restrict__ sink = nullptr)
+                                                T* __restrict__ sink = nullptr, uint32_t last_u = ~0u,
+                                                uint32_t last_v = ~0u)
 {
     constexpr int H = 32;      // positions per chunk and half; lanes per half
     constexpr int E = KP / H;  // values per lane
@@ -855,8 +857,8 @@ __device__ __forceinline__ void run_worker_half(const Sample* __restrict__ S, in
         const int mine = hi ? c1 : c0;
         const int64_t i = s0 + (hi ? f : 0) + (hl < mine ? hl : 0);
         const Sample* sp = S + (mine > 0 ? i : 0);
-        cu = __builtin_nontemporal_load(&sp->u);
-        cv = __builtin_nontemporal_load(&sp->v);
+        cu = (int)min((uint32_t)__builtin_nontemporal_load(&sp->u), last_u);
+        cv = (int)min((uint32_t)__builtin_nontemporal_load(&sp->v), last_v);
         cr = __builtin_nontemporal_load(&sp->r);
     };
 

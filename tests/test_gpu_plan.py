@@ -53,3 +53,41 @@ def test_plan_equals_the_oracles_bucketing(M, s, balance):
         got = M.debug_plan_starts(s).cpu().numpy()
         assert np.array_equal(got, start), (m, n, nnz)
         assert np.array_equal(M.debug_plan_order(nnz).cpu().numpy(), order), (m, n, nnz)
+
+
+@pytest.mark.parametrize("dtype", [0, 1])
+@pytest.mark.parametrize("nnz", [1, 63, 64, 65, 255, 257, 5003])
+def test_one_block_epoch_reads_the_callers_array(M, nnz, dtype):
+    """Batch-Hogwild! in one XCD runs on the caller's array in place: with one
+    worker it is the serial update, also of an array rewritten between two
+    epochs, and with many workers every sample is used once."""
+    m, n, k, lr, lam = 301, 103, 40, 0.01, 0.05
+    M.reset_options()
+    for key, val in dict(dtype=dtype, partition=4, workers=1).items():
+        M.set_option(key, val)
+    M.init(m, n, k, 3)
+    P, Q = oracle.init_factors(m, n, k, 3, np.float16 if dtype else np.float32)
+    d = M.samples_to_device(samples(m, n, nnz, 1, skew=False))
+    for seed in (1, 2):
+        S = samples(m, n, nnz, seed, skew=False)
+        d.copy_(M.samples_to_device(S))
+        M.epoch(d, lr, lam, lam, "hogwild")
+        oracle.epoch_serial(P, Q, S, lr, lam, lam)
+    tol = 2e-2 if dtype else 1e-4
+    for got, want in zip(M.get_factors(m, n, k), (P, Q)):
+        assert float(np.abs(got.float().cpu().numpy() - want.astype(np.float32)).max()) <= tol
+    M.set_option("workers", 0)
+    M.set_option("debug", 1)
+    M.epoch(d, lr, lam, lam, "hogwild")
+    assert bool((M.debug_visits(nnz) == 1).all())
+
+
+def test_one_block_epoch_refuses_bad_indices(M):
+    M.reset_options()
+    M.set_option("partition", 4)
+    M.init(10, 10, 8, 1)
+    S = samples(10, 10, 100, 1, skew=False)
+    S["v"][77] = 10
+    with pytest.raises(M.MfsgdError) as e:
+        M.epoch(M.samples_to_device(S), 0.01, 0.0, 0.0, "hogwild")
+    assert e.value.code == M.EINVAL
