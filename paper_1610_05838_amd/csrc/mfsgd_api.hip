@@ -125,6 +125,7 @@ struct RowStats {
     const mfsgd_sample* src = nullptr;
     int64_t nnz = -1;
     unsigned long long du = 0, dv = 0;
+    bool exact = false; // small counts too (see row_stats)
     bool matches(const mfsgd_sample* p, int64_t n) const { return src == p && nnz == n && src != nullptr; }
 };
 
@@ -155,7 +156,7 @@ struct Context {
     TablePlan gt;           // internal plan of the global scheduling table
     HotSet hot;             // hot rows of the last coherent batch-Hogwild! sample array
     RowStats stats;         // largest user and item sample counts of the last automatic batch-Hogwild! array
-    unsigned long long* maxdeg = nullptr; // 2 device words for them
+    unsigned long long* maxdeg = nullptr; // 2 device words for them, then kTopMarkWords 32-bit words
     int last_form = -1;     // form of the last batch-Hogwild! epoch (values of option "partition"), -1 before one
     int last_atomic = 0;    // whether it added its updates atomically
     int last_pairs = -1;    // whether the last block-scheduled epoch claimed two batches per wavefront, -1 before one
@@ -728,20 +729,42 @@ int bad_index_error()
     return fail(MFSGD_EINVAL, "a sample index is out of range (need 0 <= u < m and 0 <= v < n)");
 }
 
-// Largest user and item sample counts of a sample array (cached per array).
-int row_stats(const mfsgd_sample* samples, int64_t nnz, hipStream_t st)
+// Largest user and item sample counts of a sample array (cached per array):
+// exact, except that a count below kTopShare of the samples may be reported as
+// a smaller one unless `exact`.
+//
+// The automatic form needs them for its 1/64 threshold and for the cap
+// 1 / (4 lr s) on the workers, and with at most kTopWorkers resident wavefronts
+// a share s below kTopShare does not reach either while lr <= kTopMaxRate.
+// Counting every index is bound by one memory-side atomic per distinct index
+// of a 2048-sample tile (12 G samples/s: 21.6 ms of the Yahoo shape's 253 M),
+// so the indices that kTopLeast of 2^20 evenly spread samples hold are found
+// first and only those are counted in full, in one pass bound by reading the
+// samples.  A share of kTopShare gives 357 of the picks on average and fewer
+// than 256 with probability 4e-8.
+constexpr int64_t kTopPicks = int64_t(1) << 20;
+constexpr int64_t kTopLeast = 256;
+constexpr double kTopShare = 3.4e-4;
+constexpr int64_t kTopWorkers = 8192;
+constexpr float kTopMaxRate = (float)(0.25 / (kTopShare * kTopWorkers)); // 0.0897
+
+int row_stats(const mfsgd_sample* samples, int64_t nnz, bool exact, hipStream_t st)
 {
     Context& c = g;
-    if (c.stats.matches(samples, nnz))
+    if (c.stats.matches(samples, nnz) && (c.stats.exact || !exact))
         return MFSGD_OK;
     c.stats.src = nullptr;
     CHK(grow(&c.deg, &c.deg_cap, c.m + c.n, "plan degrees"));
     if (!c.maxdeg)
-        CHK(dalloc((void**)&c.maxdeg, 2 * sizeof(unsigned long long), "largest degrees"));
+        CHK(dalloc((void**)&c.maxdeg, 2 * sizeof(unsigned long long) + kTopMarkWords * sizeof(uint32_t),
+                   "largest degrees"));
+    uint32_t* marks = (uint32_t*)(c.maxdeg + 2);
+    const bool all = exact || nnz <= 4 * kTopPicks;
     HIPCHK(hipMemsetAsync(c.bad, 0, sizeof(int), st));
     HIPCHK(hipMemsetAsync(c.deg, 0, sizeof(unsigned long long) * (size_t)(c.m + c.n), st));
-    HIPCHK(hipMemsetAsync(c.maxdeg, 0, 2 * sizeof(unsigned long long), st));
-    HIPCHK(plan_degrees((const Sample*)samples, nnz, nnz, c.m, c.n, c.deg, c.deg + c.m, c.bad, st));
+    HIPCHK(hipMemsetAsync(c.maxdeg, 0, 2 * sizeof(unsigned long long) + kTopMarkWords * sizeof(uint32_t), st));
+    HIPCHK(top_degrees((const Sample*)samples, nnz, all ? nnz : kTopPicks, kTopLeast, c.m, c.n, c.deg, c.deg + c.m,
+                       marks, c.bad, st));
     HIPCHK(max_degree(c.deg, c.m, c.maxdeg, st));
     HIPCHK(max_degree(c.deg + c.m, c.n, c.maxdeg + 1, st));
     unsigned long long h[2] = {0, 0};
@@ -754,6 +777,7 @@ int row_stats(const mfsgd_sample* samples, int64_t nnz, hipStream_t st)
     }
     c.stats.du = h[0];
     c.stats.dv = h[1];
+    c.stats.exact = all;
     c.stats.src = samples;
     c.stats.nnz = nnz;
     return MFSGD_OK;
@@ -896,7 +920,7 @@ int build_plan(Plan& pl, const mfsgd_sample* samples, int64_t nnz, int s, bool b
 // 107 ms first epoch and 150 us of a 4,001-rating batch's 530 us.
 int whole_plan(Plan& pl, const mfsgd_sample* samples, int64_t nnz, hipStream_t st)
 {
-    CHK(row_stats(samples, nnz, st));
+    CHK(row_stats(samples, nnz, false, st)); // shares near a half decide the hot-row measures
     if (!pl.bstart)
         CHK(dalloc((void**)&pl.bstart, sizeof(int64_t) * (kMaxGrid * kMaxGrid + 1), "plan starts"));
     if (!pl.whole || pl.hstart.size() != 2 || pl.hstart[1] != nnz) {
@@ -1282,7 +1306,7 @@ int epoch_impl(const mfsgd_sample* samples, int64_t nnz, float lr, float lp, flo
     bool atomic = hog && g_opt.atomic != 0;
     if (automatic) {
         // the serial-tracking form for these samples
-        CHK(row_stats(samples, nnz, st));
+        CHK(row_stats(samples, nnz, !(std::fabs(lr) <= kTopMaxRate) || 32 * (int64_t)c.cus > kTopWorkers, st));
         const unsigned long long top = std::max(c.stats.du, c.stats.dv);
         const bool skewed = nnz > 0 && (double)top * kOneXcdShareInv > (double)nnz;
         // atomic adds need one worker per wavefront and, in binary16, value pairs

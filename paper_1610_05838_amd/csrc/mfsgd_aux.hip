@@ -1,5 +1,7 @@
 // mfsgd_aux.hip -- storage-type independent kernels: RMSE final reduction,
 // index checks, ticket reset and the wavefront-update planner.
+#include <algorithm>
+
 #include "mfsgd_device.hpp"
 #include "mfsgd_launch.hpp"
 
@@ -224,17 +226,41 @@ __device__ __forceinline__ int64_t pick_position(int64_t i, int64_t picks, int64
     return lo + (int64_t)(((sm64_at(0, (uint64_t)i) >> 32) * (uint64_t)(hi - lo)) >> 32);
 }
 
-__global__ __launch_bounds__(256) void k_degrees(const Sample* __restrict__ S, int64_t nnz, int64_t picks, int64_t m,
-                                                 int64_t n, unsigned long long* __restrict__ du,
-                                                 unsigned long long* __restrict__ dv, int* bad)
+// MARKED: only the indices whose bit is set in the marks (one bit per hash
+// value: a marked index's samples are all counted, an unmarked one's never or
+// all, by chance of its hash).  Indices out of range are flagged either way.
+constexpr int kMarkBits = 17; // 16 KB of LDS per side
+constexpr int kMarkWords = 1 << (kMarkBits - 5);
+
+__device__ __forceinline__ unsigned mark_hash(int i) { return ((unsigned)i * 2246822519u) >> (32 - kMarkBits); }
+
+template <bool MARKED>
+__global__ __launch_bounds__(MARKED ? 512 : 256) void k_degrees(const Sample* __restrict__ S, int64_t nnz,
+                                                               int64_t picks, int64_t m, int64_t n,
+                                                               const uint32_t* __restrict__ marks,
+                                                               unsigned long long* __restrict__ du,
+                                                               unsigned long long* __restrict__ dv, int* bad)
 {
     __shared__ int ku[kDegSlots], kv[kDegSlots];
     __shared__ unsigned cu[kDegSlots], cv[kDegSlots];
+    __shared__ uint32_t mu[MARKED ? kMarkWords : 1], mv[MARKED ? kMarkWords : 1];
+    __shared__ int dirty; // whether the tile put anything into the tables
     for (int j = threadIdx.x; j < kDegSlots; j += blockDim.x) {
         ku[j] = kv[j] = -1;
         cu[j] = cv[j] = 0u;
     }
+    if constexpr (MARKED)
+        for (int j = threadIdx.x; j < kMarkWords; j += blockDim.x) {
+            mu[j] = marks[j];
+            mv[j] = marks[kMarkWords + j];
+        }
+    if (threadIdx.x == 0)
+        dirty = 0;
     __syncthreads();
+    auto marked = [](const uint32_t* w, int i) {
+        const unsigned h = mark_hash(i);
+        return ((w[h >> 5] >> (h & 31)) & 1u) != 0;
+    };
     int found = 0;
     const int64_t tiles = (picks + kDegTile - 1) / kDegTile;
     for (int64_t t = blockIdx.x; t < tiles; t += gridDim.x) {
@@ -248,26 +274,51 @@ __global__ __launch_bounds__(256) void k_degrees(const Sample* __restrict__ S, i
                 found = 1;
                 continue;
             }
-            deg_insert(ku, cu, u);
-            deg_insert(kv, cv, v);
+            if (!MARKED || marked(mu, u)) {
+                deg_insert(ku, cu, u);
+                dirty = 1;
+            }
+            if (!MARKED || marked(mv, v)) {
+                deg_insert(kv, cv, v);
+                dirty = 1;
+            }
         }
         __syncthreads();
-        for (int j = threadIdx.x; j < kDegSlots; j += blockDim.x) {
-            if (ku[j] >= 0) {
-                atomicAdd(du + ku[j], (unsigned long long)cu[j]);
-                ku[j] = -1;
-                cu[j] = 0u;
+        if (dirty)
+            for (int j = threadIdx.x; j < kDegSlots; j += blockDim.x) {
+                if (ku[j] >= 0) {
+                    atomicAdd(du + ku[j], (unsigned long long)cu[j]);
+                    ku[j] = -1;
+                    cu[j] = 0u;
+                }
+                if (kv[j] >= 0) {
+                    atomicAdd(dv + kv[j], (unsigned long long)cv[j]);
+                    kv[j] = -1;
+                    cv[j] = 0u;
+                }
             }
-            if (kv[j] >= 0) {
-                atomicAdd(dv + kv[j], (unsigned long long)cv[j]);
-                kv[j] = -1;
-                cv[j] = 0u;
-            }
-        }
+        __syncthreads();
+        if (threadIdx.x == 0)
+            dirty = 0;
         __syncthreads();
     }
     if (found)
         atomicOr(bad, 1);
+}
+
+// Marks every index counted at least `least` times and clears the counts.
+__global__ void k_mark(unsigned long long* __restrict__ deg, int64_t rows, unsigned long long least,
+                       uint32_t* __restrict__ marks)
+{
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < rows; i += (int64_t)gridDim.x * blockDim.x) {
+        const unsigned long long d = deg[i];
+        if (d >= least) {
+            const unsigned h = mark_hash((int)i);
+            atomicOr(marks + (h >> 5), 1u << (h & 31));
+        }
+        if (d)
+            deg[i] = 0;
+    }
 }
 
 // Samples of every row block and column block, and the most any one index of
@@ -381,7 +432,25 @@ hipError_t plan_degrees(const Sample* S, int64_t nnz, int64_t picks, int64_t m, 
     int64_t blocks = (picks + kDegTile - 1) / kDegTile;
     if (blocks > 2048)
         blocks = 2048;
-    hipLaunchKernelGGL(k_degrees, dim3((unsigned)blocks), dim3(256), 0, st, S, nnz, picks, m, n, du, dv, bad);
+    hipLaunchKernelGGL(k_degrees<false>, dim3((unsigned)blocks), dim3(256), 0, st, S, nnz, picks, m, n,
+                       (const uint32_t*)nullptr, du, dv, bad);
+    return hipGetLastError();
+}
+
+hipError_t top_degrees(const Sample* S, int64_t nnz, int64_t picks, int64_t least, int64_t m, int64_t n,
+                       unsigned long long* du, unsigned long long* dv, uint32_t* marks, int* bad, hipStream_t st)
+{
+    static_assert(2 * kMarkWords == kTopMarkWords, "marks of users, then of items");
+    hipError_t e = plan_degrees(S, nnz, picks, m, n, du, dv, bad, st);
+    if (e != hipSuccess || picks >= nnz)
+        return e;
+    const int64_t blocks = std::min<int64_t>((nnz + kDegTile - 1) / kDegTile, 2048);
+    hipLaunchKernelGGL(k_mark, dim3((unsigned)std::min<int64_t>((m + 255) / 256, 2048)), dim3(256), 0, st, du, m,
+                       (unsigned long long)least, marks);
+    hipLaunchKernelGGL(k_mark, dim3((unsigned)std::min<int64_t>((n + 255) / 256, 2048)), dim3(256), 0, st, dv, n,
+                       (unsigned long long)least, marks + kMarkWords);
+    hipLaunchKernelGGL(k_degrees<true>, dim3((unsigned)blocks), dim3(512), 0, st, S, nnz, nnz, m, n,
+                       (const uint32_t*)marks, du, dv, bad);
     return hipGetLastError();
 }
 

@@ -143,6 +143,13 @@ struct PlanBuffers {
 // of `picks` < nnz of them spread evenly over the array
 hipError_t plan_degrees(const Sample* S, int64_t nnz, int64_t picks, int64_t m, int64_t n, unsigned long long* du,
                         unsigned long long* dv, int* bad, hipStream_t st);
+// the exact counts of every index that at least `least` of `picks` evenly
+// spread samples hold (and of some others; 0 for the rest); of all indices when
+// picks >= nnz.  The counts and the kTopMarkWords words of `marks` are zero at
+// entry.
+constexpr int kTopMarkWords = 8192;
+hipError_t top_degrees(const Sample* S, int64_t nnz, int64_t picks, int64_t least, int64_t m, int64_t n,
+                       unsigned long long* du, unsigned long long* dv, uint32_t* marks, int* bad, hipStream_t st);
 // out[2 j], out[2 j + 1] = samples and largest count of one index, for the s
 // row blocks (users rbnd[j] .. rbnd[j+1]-1), then the s column blocks
 hipError_t block_tops(const unsigned long long* du, const unsigned long long* dv, const int64_t* rbnd,

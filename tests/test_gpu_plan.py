@@ -91,3 +91,26 @@ def test_one_block_epoch_refuses_bad_indices(M):
     with pytest.raises(M.MfsgdError) as e:
         M.epoch(M.samples_to_device(S), 0.01, 0.0, 0.0, "hogwild")
     assert e.value.code == M.EINVAL
+
+
+@pytest.mark.parametrize("share, form", [(1 / 60, 4), (1 / 70, 0)])
+def test_automatic_form_on_large_arrays(M, share, form):
+    """The largest row's share decides the automatic form (1/64); on arrays
+    above 2^22 samples only rows that a subsample marks are counted in full."""
+    import torch
+    m, n, nnz = 300_007, 200_003, (1 << 22) + 12_345
+    M.reset_options()
+    M.init(m, n, 64, 1)
+    g = torch.Generator(device="cuda").manual_seed(5)
+    S = torch.empty((nnz, 3), dtype=torch.int32, device="cuda")
+    S[:, 0] = torch.randint(0, m, (nnz,), device="cuda", generator=g, dtype=torch.int32)
+    S[:, 1] = torch.randint(0, n, (nnz,), device="cuda", generator=g, dtype=torch.int32)
+    S[:int(nnz * share), 1] = 123_456  # all in one place of the array
+    S[:, 2] = 0
+    M.epoch(S, 0.001, 0.01, 0.01, "hogwild")
+    assert M.get_option("hogwild_form") == form
+    S[-1, 0] = m  # one bad index anywhere is found, marked row or not
+    other = S.clone()
+    with pytest.raises(M.MfsgdError) as e:
+        M.epoch(other, 0.001, 0.01, 0.01, "hogwild")
+    assert e.value.code == M.EINVAL
