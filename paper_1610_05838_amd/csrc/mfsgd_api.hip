@@ -1530,14 +1530,23 @@ int epoch_impl(const mfsgd_sample* samples, int64_t nnz, float lr, float lp, flo
 // ---------------------------------------------------------------------------
 // staged epochs (samples in host memory)
 // ---------------------------------------------------------------------------
-// The sample array is cut into chunks of C consecutive samples (C = option
-// "stage_samples" rounded down to a multiple of f).  Chunk i is copied into
+// The sample array is cut into chunks of C consecutive samples, C at most
+// option "stage_samples", a multiple of f.  The first copy and the last kernel
+// overlap with nothing, so chunks are no larger than they need to be: one
+// batch for every worker, and at least kStageLeast samples, below which the
+// cost of a copy and a launch shows (19.8 M binary32 samples at k = 128, pinned:
+// 11.5 / 5.1 / 4.8 / 4.7 / 4.9 / 5.7 ms an epoch in chunks of 2^18 / 2^19 /
+// 2^20 / 2^21 / 2^22 / 2^23, 7.8 ms in one chunk; the copy alone is 4.3 ms at
+// 55 GB/s of PCIe, which bounds it).  Chunk i is copied into
 // device buffer i mod 3 on the library's copy stream while the caller's
 // stream runs the batch-Hogwild! kernel (one address space) over chunk i-1;
 // events order each copy after the kernel that last read its buffer and
 // each kernel after its copy.  A pinned caller array is copied directly; a
 // pageable one passes through pinned staging buffers, filled by this thread
 // once the copy that last read them has finished.
+constexpr int64_t kStageLeast = int64_t(1) << 21;
+constexpr int64_t kStageMost = int64_t(1) << 31; // the largest "stage_samples"
+
 int staged_buffers(int64_t C, bool pageable)
 {
     Context& c = g;
@@ -1602,7 +1611,6 @@ int epoch_staged_impl(const mfsgd_sample* samples, int64_t nnz, float lr, float 
         }
     }
     const int64_t f = g_opt.batch_f;
-    const int64_t C = std::max<int64_t>(f, g_opt.stage_samples / f * f);
     const int64_t dbg = g_opt.debug;
     EpochLaunch a{};
     a.scheme = kSchemeHogwild;
@@ -1624,6 +1632,8 @@ int epoch_staged_impl(const mfsgd_sample* samples, int64_t nnz, float lr, float 
         W = (int64_t)c.cus * per_cu * (half_wave_workers(c.KP, c.dtype) ? 2 : 1);
     }
     a.half = half_wave_workers(c.KP, c.dtype) ? 1 : 0;
+    const int64_t cap = std::min(std::max(kStageLeast, W > kStageMost / f ? kStageMost : W * f), g_opt.stage_samples);
+    const int64_t C = std::max<int64_t>(f, cap / f * f);
     if (dbg & 1) {
         CHK(grow(&c.visits, &c.visits_cap, nnz, "visit counters"));
         c.visits_n = nnz;

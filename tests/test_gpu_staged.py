@@ -90,6 +90,21 @@ def test_staged_coverage(M, pinned):
         assert np.all(M.debug_visits(nnz).cpu().numpy() == 1)
 
 
+@pytest.mark.parametrize("dtype, k, pinned", [(np.float32, 64, True), (np.float16, 32, True), (np.float32, 16, False)])
+@pytest.mark.parametrize("nnz", [(1 << 21) - 1, 1 << 21, (1 << 21) + 1, 9 * (1 << 21) + 77])
+def test_staged_default_chunks_cover(M, nnz, dtype, k, pinned):
+    """The default chunks (2^21 samples, or one batch per worker where that
+    is more), around one chunk and past a reuse of all three buffers: every
+    sample is used exactly once."""
+    rng = np.random.default_rng(nnz)
+    S = rand_samples(rng, 3000, 2000, nnz)
+    setup(M, 3000, 2000, k, 3, dtype, debug=1)
+    H = host(S, True) if pinned else S  # kept until the copies are done
+    for _ in range(2):
+        M.epoch_staged(H, 0.0001, 0.05, 0.05)
+        assert bool((M.debug_visits(nnz) == 1).all())
+
+
 def test_staged_lr_zero_is_identity(M):
     import torch
     rng = np.random.default_rng(6)
