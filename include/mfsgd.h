@@ -103,7 +103,9 @@ enum {
      *   3 as 1 without the column tickets (the fastest form): workers that
      *     drift apart may share a column block across XCDs.
      *   4 one XCD: the whole array as one block run by the wavefronts of one
-     *     XCD (a 1 x 1 grid), claiming batches in order. */
+     *     XCD (a 1 x 1 grid), claiming batches in order.  No copy is made:
+     *     every epoch reads the caller's array as it then is (see
+     *     mfsgd_epoch). */
     MFSGD_BATCH_HOGWILD = 0,
     /* wavefront-update (section 3.2.3) on the s x s grid of the last
      * mfsgd_plan: worker i owns row block i and visits the column blocks in
@@ -320,6 +322,13 @@ int mfsgd_plan(const mfsgd_sample* samples, int64_t nnz, int32_t s, void* stream
  * keys the per-epoch column orders.  Indices are not checked by the
  * one-address-space batch-Hogwild! (use mfsgd_check_samples): an index out
  * of range is undefined behaviour there.
+ * A sample array is known by its address and length: forms 1 and 3 and the
+ * global table keep a copy made on its first epoch and train on that.  The
+ * one-XCD form (and form 0) reads the array itself, so ratings written over it
+ * since are trained on; the one-XCD form's first epoch checks the indices
+ * synchronously (EINVAL), every later one on the stream: an index out of range
+ * then makes that epoch do nothing, and the next call that synchronises
+ * returns EINVAL.
  * EINVAL: nnz < 0, NULL samples with nnz > 0, unknown scheme, non-finite lr
  * or lambda, (planning) an index out of range, or nnz >= 2^32 for
  * MFSGD_GLOBAL_TABLE.  ESTATE: no init, or a
@@ -354,7 +363,8 @@ int mfsgd_epoch_staged(const mfsgd_sample* samples, int64_t nnz, float lr, float
  * (r - p_u . q_v)^2 / ntest), dot products in binary32, squares summed in
  * binary64 in a fixed order (the result is reproducible bit for bit); 0 for
  * ntest == 0.  Synchronises `stream` and writes *rmse_out.  Also reports a
- * pending device error (ETIMEOUT) of earlier work on the stream.
+ * pending device error (ETIMEOUT, EINVAL; see mfsgd_sync) of earlier work on
+ * the stream.
  * ENUMERIC: the result is not finite (it is still written). */
 int mfsgd_rmse(const mfsgd_sample* test, int64_t ntest, double* rmse_out, void* stream);
 
@@ -381,7 +391,9 @@ int mfsgd_rmse_noalloc(const mfsgd_sample* test, int64_t ntest, double* rmse_dev
 int mfsgd_check_samples(const mfsgd_sample* samples, int64_t nnz, void* stream);
 
 /* Wait for `stream` and report a device-side error of earlier epochs
- * (MFSGD_ETIMEOUT if a ticket wait gave up; the flag is then cleared). */
+ * (MFSGD_ETIMEOUT if a ticket wait gave up, MFSGD_EINVAL if a one-XCD epoch
+ * met an index out of range in an array rewritten since its first epoch and
+ * made no update; the flag is then cleared). */
 int mfsgd_sync(void* stream);
 
 /* Copy the factors out / in, compact m x k and n x k row-major in the

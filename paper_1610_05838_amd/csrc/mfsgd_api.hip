@@ -145,12 +145,13 @@ struct Context {
     uint32_t* prio = nullptr; // kMaxGrid^2: critical-path weight per (team, wave) of the last pooled epoch
     int prio_s = 0;           // its grid side (0: none yet)
     uint32_t* sched = nullptr; // block-scheduled claim state (kSchedWords)
-    int* err = nullptr;
+    int* err = nullptr; // 2 words: a ticket wait gave up; an index out of range stopped a one-XCD epoch
+    int64_t* one = nullptr; // block starts of the one-block grid, written by every such epoch
     int* bad = nullptr;
     double* partial = nullptr;
     double* dres = nullptr;
     double* hres = nullptr; // pinned
-    int* hflag = nullptr;   // pinned
+    int* hflag = nullptr;   // pinned, 2 words
     Plan wf;                // the caller's wavefront-update plan (mfsgd_plan)
     Plan hw;                // internal plan of the XCD-partitioned batch-Hogwild!
     TablePlan gt;           // internal plan of the global scheduling table
@@ -292,6 +293,7 @@ void release_all()
     dfree(c.prio);
     dfree(c.sched);
     dfree(c.err);
+    dfree(c.one);
     dfree(c.bad);
     dfree(c.partial);
     dfree(c.dres);
@@ -373,21 +375,24 @@ int occupancy_blocked(int KP, int dtype, int depth, int threads, bool half = fal
                                : occupancy_blocked_f32(KP, depth, threads, half ? 1 : 0);
 }
 
-// Read back and clear the device error flag; the stream has been synchronised.
+// Read back and clear the device error flags; the stream has been synchronised.
 int take_device_error()
 {
-    if (*g.hflag) {
-        *g.hflag = 0;
-        int zero = 0;
-        HIPCHK(hipMemcpy(g.err, &zero, sizeof(int), hipMemcpyHostToDevice));
+    const bool late = g.hflag[0] != 0, bad = g.hflag[1] != 0;
+    if (!late && !bad)
+        return MFSGD_OK;
+    g.hflag[0] = g.hflag[1] = 0;
+    const int zero[2] = {0, 0};
+    HIPCHK(hipMemcpy(g.err, zero, sizeof(zero), hipMemcpyHostToDevice));
+    if (late)
         return fail(MFSGD_ETIMEOUT, "a block-schedule ticket wait exceeded spin_limit; the epoch was abandoned");
-    }
-    return MFSGD_OK;
+    return fail(MFSGD_EINVAL, "a sample index was out of range in an array rewritten since its first epoch; that "
+                              "epoch made no update");
 }
 
 int sync_and_check(hipStream_t st)
 {
-    HIPCHK(hipMemcpyAsync(g.hflag, g.err, sizeof(int), hipMemcpyDeviceToHost, st));
+    HIPCHK(hipMemcpyAsync(g.hflag, g.err, 2 * sizeof(int), hipMemcpyDeviceToHost, st));
     HIPCHK(hipStreamSynchronize(st));
     return take_device_error();
 }
@@ -629,7 +634,8 @@ int init_impl(int64_t m, int64_t n, int32_t k, uint64_t seed)
         (rc = dalloc((void**)&c.tickets, sizeof(uint32_t) * kMaxGrid, "tickets")) ||
         (rc = dalloc((void**)&c.prio, sizeof(uint32_t) * kMaxGrid * kMaxGrid, "block priorities")) ||
         (rc = dalloc((void**)&c.sched, sizeof(uint32_t) * kSchedWords, "claim counters")) ||
-        (rc = dalloc((void**)&c.err, sizeof(int), "flag")) || (rc = dalloc((void**)&c.bad, sizeof(int), "flag")) ||
+        (rc = dalloc((void**)&c.err, 2 * sizeof(int), "flag")) ||
+        (rc = dalloc((void**)&c.one, 2 * sizeof(int64_t), "one block's starts")) || (rc = dalloc((void**)&c.bad, sizeof(int), "flag")) ||
         (rc = dalloc((void**)&c.partial, sizeof(double) * kRmseWaves, "rmse partials")) ||
         (rc = dalloc((void**)&c.dres, sizeof(double), "rmse result")) ||
         (rc = dalloc((void**)&c.bnd, sizeof(int64_t) * 2 * (kMaxGrid + 1), "plan bounds"))) {
@@ -637,15 +643,15 @@ int init_impl(int64_t m, int64_t n, int32_t k, uint64_t seed)
         return rc;
     }
     if (hipHostMalloc((void**)&c.hres, sizeof(double), hipHostMallocDefault) != hipSuccess ||
-        hipHostMalloc((void**)&c.hflag, sizeof(int), hipHostMallocDefault) != hipSuccess) {
+        hipHostMalloc((void**)&c.hflag, 2 * sizeof(int), hipHostMallocDefault) != hipSuccess) {
         (void)hipGetLastError();
         release_all();
         return fail(MFSGD_ENOMEM, "pinned host allocation failed");
     }
-    *c.hflag = 0;
-    HIPCHK(hipMemset(c.err, 0, sizeof(int)));
+    c.hflag[0] = c.hflag[1] = 0;
+    HIPCHK(hipMemset(c.err, 0, 2 * sizeof(int)));
     HIPCHK(hipMemset(c.bad, 0, sizeof(int)));
-    HIPCHK(reset_tickets(c.tickets, c.sched, nullptr));
+    HIPCHK(reset_tickets(c.tickets, c.sched, nullptr, 0, nullptr));
     const double inv_sqrt_k = 1.0 / std::sqrt((double)k);
     const uint64_t sp = sm64_at(seed, kTagP), sq = sm64_at(seed, kTagQ);
     if (c.dtype == MFSGD_FP16) {
@@ -748,7 +754,8 @@ constexpr double kTopShare = 3.4e-4;
 constexpr int64_t kTopWorkers = 8192;
 constexpr float kTopMaxRate = (float)(0.25 / (kTopShare * kTopWorkers)); // 0.0897
 
-int row_stats(const mfsgd_sample* samples, int64_t nnz, bool exact, hipStream_t st)
+// *seen is set if this call read the samples and found every index in range.
+int row_stats(const mfsgd_sample* samples, int64_t nnz, bool exact, bool* seen, hipStream_t st)
 {
     Context& c = g;
     if (c.stats.matches(samples, nnz) && (c.stats.exact || !exact))
@@ -780,6 +787,7 @@ int row_stats(const mfsgd_sample* samples, int64_t nnz, bool exact, hipStream_t 
     c.stats.exact = all;
     c.stats.src = samples;
     c.stats.nnz = nnz;
+    *seen = true;
     return MFSGD_OK;
 }
 
@@ -917,18 +925,13 @@ int build_plan(Plan& pl, const mfsgd_sample* samples, int64_t nnz, int s, bool b
 // array as it stands, so nothing is sorted or copied, and the epoch reads the
 // array itself; only the index check and the hot-row measures are taken.  The
 // copy and the second counting pass took 9.5 ms of the Netflix shape's
-// 107 ms first epoch and 150 us of a 4,001-rating batch's 530 us.
-int whole_plan(Plan& pl, const mfsgd_sample* samples, int64_t nnz, hipStream_t st)
+// 107 ms first epoch and 150 us of a 4,001-rating batch's 530 us.  The block's
+// bounds belong to the launch, not to the plan (Context::one): a captured
+// epoch keeps its own.
+int whole_plan(Plan& pl, const mfsgd_sample* samples, int64_t nnz, bool* seen, hipStream_t st)
 {
-    CHK(row_stats(samples, nnz, false, st)); // shares near a half decide the hot-row measures
-    if (!pl.bstart)
-        CHK(dalloc((void**)&pl.bstart, sizeof(int64_t) * (kMaxGrid * kMaxGrid + 1), "plan starts"));
-    if (!pl.whole || pl.hstart.size() != 2 || pl.hstart[1] != nnz) {
-        pl.invalidate();
-        pl.hstart.assign({0, nnz});
-        HIPCHK(hipMemcpyAsync(pl.bstart, pl.hstart.data(), 2 * sizeof(int64_t), hipMemcpyHostToDevice, st));
-        HIPCHK(hipStreamSynchronize(st));
-    }
+    CHK(row_stats(samples, nnz, false, seen, st)); // shares near a half decide the hot-row measures
+    pl.hstart.assign({0, nnz});
     if (!pl.whole)
         pl.version += 1; // another layout; one block's does not depend on the samples
     pl.src = samples;
@@ -1099,7 +1102,7 @@ int check_impl(const mfsgd_sample* samples, int64_t nnz, hipStream_t st)
     if (nnz == 0)
         return MFSGD_OK;
     HIPCHK(hipMemsetAsync(g.bad, 0, sizeof(int), st));
-    HIPCHK(check_indices((const Sample*)samples, nnz, g.m, g.n, g.bad, st));
+    HIPCHK(check_indices((const Sample*)samples, nnz, g.m, g.n, g.bad, nullptr, st));
     HIPCHK(hipMemcpyAsync(g.hflag, g.bad, sizeof(int), hipMemcpyDeviceToHost, st));
     HIPCHK(hipStreamSynchronize(st));
     const int bad = *g.hflag;
@@ -1304,9 +1307,10 @@ int epoch_impl(const mfsgd_sample* samples, int64_t nnz, float lr, float lp, flo
     const bool automatic = hog && g_opt.partition == 2;
     int form = hog ? (int)g_opt.partition : -1;
     bool atomic = hog && g_opt.atomic != 0;
+    bool seen = false; // this call has read the samples and found every index in range
     if (automatic) {
         // the serial-tracking form for these samples
-        CHK(row_stats(samples, nnz, !(std::fabs(lr) <= kTopMaxRate) || 32 * (int64_t)c.cus > kTopWorkers, st));
+        CHK(row_stats(samples, nnz, !(std::fabs(lr) <= kTopMaxRate) || 32 * (int64_t)c.cus > kTopWorkers, &seen, st));
         const unsigned long long top = std::max(c.stats.du, c.stats.dv);
         const bool skewed = nnz > 0 && (double)top * kOneXcdShareInv > (double)nnz;
         // atomic adds need one worker per wavefront and, in binary16, value pairs
@@ -1325,7 +1329,7 @@ int epoch_impl(const mfsgd_sample* samples, int64_t nnz, float lr, float lp, flo
         const bool keep = (dbg & 1) != 0;
         if (s_h == 1) {
             if (!c.hw.matches(samples, nnz) || !c.hw.whole)
-                CHK(whole_plan(c.hw, samples, nnz, st));
+                CHK(whole_plan(c.hw, samples, nnz, &seen, st));
         } else if (!c.hw.matches(samples, nnz) || c.hw.s != s_h || c.hw.balanced != balanced_grid(s_h) ||
             (keep && !c.hw.has_orig))
             CHK(build_plan(c.hw, samples, nnz, s_h, balanced_grid(s_h), keep, st));
@@ -1441,7 +1445,7 @@ int epoch_impl(const mfsgd_sample* samples, int64_t nnz, float lr, float lp, flo
         a.S = pl->whole ? (const Sample*)samples : pl->Sp;
         a.last_u = (uint32_t)(c.m - 1);
         a.last_v = (uint32_t)(c.n - 1);
-        a.bstart = pl->bstart;
+        a.bstart = pl->whole ? c.one : pl->bstart;
         a.s = s;
         // Pooled wavefronts that claim two batches at a time and run one per
         // half: block-scheduled batch-Hogwild! at k <= 32, in place of
@@ -1482,6 +1486,14 @@ int epoch_impl(const mfsgd_sample* samples, int64_t nnz, float lr, float lp, flo
         }
         a.sigma_c = sm64_at(c.seed, kTagColPerm + 2ull * (uint64_t)c.epoch);
         a.sigma_o = sm64_at(c.seed, kTagWaveOffset + 2ull * (uint64_t)c.epoch);
+        if (!(scheme == MFSGD_WAVEFRONT_DET && g_opt.wave_launch))
+            HIPCHK(reset_tickets(c.tickets, c.sched, pl->whole ? c.one : nullptr, nnz, st));
+        // The caller's own array is read again by every epoch, so its indices
+        // are checked again before each (on the stream, nothing is waited
+        // for: 0.25 ms before the Netflix shape's 91 ms); a bad one closes
+        // the gate, and the next synchronising call reports it.
+        if (pl->whole && !seen)
+            HIPCHK(check_indices((const Sample*)samples, nnz, c.m, c.n, (int*)c.sched + kSchedGate, c.err + 1, st));
         a.prio = nullptr;
         if (a.pool && g_opt.priority) {
             HIPCHK(block_priority(a.bstart, s, a.sigma_c, a.sigma_o, c.prio, st));
@@ -1511,7 +1523,6 @@ int epoch_impl(const mfsgd_sample* samples, int64_t nnz, float lr, float lp, flo
                     HIPCHK(epoch_f32(a, st));
             }
         } else {
-            HIPCHK(reset_tickets(c.tickets, c.sched, st));
             if (c.dtype == MFSGD_FP16)
                 HIPCHK(epoch_f16(a, st));
             else

@@ -34,7 +34,7 @@ hipError_t rmse_final(const double* partial, int64_t ntest, double* out, hipStre
     return hipGetLastError();
 }
 
-__global__ void k_check(const Sample* __restrict__ S, int64_t nnz, int64_t m, int64_t n, int* bad)
+__global__ void k_check(const Sample* __restrict__ S, int64_t nnz, int64_t m, int64_t n, int* bad, int* too)
 {
     int found = 0;
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < nnz; i += (int64_t)gridDim.x * blockDim.x) {
@@ -42,33 +42,38 @@ __global__ void k_check(const Sample* __restrict__ S, int64_t nnz, int64_t m, in
         const int v = __builtin_nontemporal_load(&S[i].v);
         found |= (u < 0) | (u >= m) | (v < 0) | (v >= n);
     }
-    if (found)
+    if (found) {
         atomicOr(bad, 1);
+        if (too)
+            atomicOr(too, 1);
+    }
 }
 
-hipError_t check_indices(const Sample* S, int64_t nnz, int64_t m, int64_t n, int* bad, hipStream_t st)
+hipError_t check_indices(const Sample* S, int64_t nnz, int64_t m, int64_t n, int* bad, int* too, hipStream_t st)
 {
     if (nnz <= 0)
         return hipSuccess;
     int64_t blocks = (nnz + 255) / 256;
     if (blocks > 8192)
         blocks = 8192;
-    hipLaunchKernelGGL(k_check, dim3((unsigned)blocks), dim3(256), 0, st, S, nnz, m, n, bad);
+    hipLaunchKernelGGL(k_check, dim3((unsigned)blocks), dim3(256), 0, st, S, nnz, m, n, bad, too);
     return hipGetLastError();
 }
 
-__global__ void k_reset_tickets(uint32_t* tickets, uint32_t* sched)
+__global__ void k_reset_tickets(uint32_t* tickets, uint32_t* sched, int64_t* one, int64_t nnz)
 {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i < kMaxGrid)
         tickets[i] = 0u;
     if (i < kSchedWords)
         sched[i] = 0u;
+    if (one && i < 2)
+        one[i] = i ? nnz : 0;
 }
 
-hipError_t reset_tickets(uint32_t* tickets, uint32_t* sched, hipStream_t st)
+hipError_t reset_tickets(uint32_t* tickets, uint32_t* sched, int64_t* one, int64_t nnz, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_reset_tickets, dim3((kSchedWords + 255) / 256), dim3(256), 0, st, tickets, sched);
+    hipLaunchKernelGGL(k_reset_tickets, dim3((kSchedWords + 255) / 256), dim3(256), 0, st, tickets, sched, one, nnz);
     return hipGetLastError();
 }
 

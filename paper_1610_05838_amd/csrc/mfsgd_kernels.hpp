@@ -98,7 +98,10 @@ __global__ __launch_bounds__(kHogwildBlock) void k_hogwild_half(const Sample* __
 // sched: [0, G2) units finished per (team, wave), [G2, 2 G2) head claims
 // taken per (team, wave), [2 G2, 2 G2 + kMaxGrid) cursor per team, one event
 // counter, kMaxGrid workgroups arrived per XCD, then [.., + G2) unit claims
-// taken per (team, wave), where G2 = kMaxGrid^2; all zero at launch.
+// taken per (team, wave), where G2 = kMaxGrid^2, then the gate; all zero at
+// launch but the gate, which the index check that runs before the epoch on the
+// same stream sets if the samples may not be trained on: every workgroup then
+// leaves at once.
 //
 // Debug (trace != nullptr): trace[t*s + w] = column of team t in wave w, and
 // after those s*s entries two stamps per (team, wave) from the event counter:
@@ -137,6 +140,7 @@ __global__ __launch_bounds__(256) void k_blocked(const Sample* __restrict__ Sp, 
     __shared__ int s_tm, s_x;
     uint32_t* const arrived = sched + 2 * kMaxGrid * kMaxGrid + kMaxGrid + 1;
     if (threadIdx.x == 0) {
+        const uint32_t shut = __hip_atomic_load(sched + kSchedGate, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (xslots > 0) {
             // pooled teams: the XCD this workgroup runs on (hardware register)
             // and its arrival order there select its team, so a team's
@@ -152,6 +156,8 @@ __global__ __launch_bounds__(256) void k_blocked(const Sample* __restrict__ Sp, 
             s_x = 0;
             s_tm = tmap[blockIdx.x];
         }
+        if (shut)
+            s_tm = -1;
         shuffle_perm(sigma_c, s, Cperm);
         shuffle_perm(sigma_o, s, Ooff);
     }

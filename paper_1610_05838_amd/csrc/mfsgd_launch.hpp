@@ -16,7 +16,8 @@ constexpr int kSchemeWavefront = 1;
 constexpr int kSchemeWaveLaunch = 2; // one deterministic wavefront-update wave per launch (cross-check)
 // block-scheduled claim state: finished units and head claims per (team, wave), cursor per team, event counter,
 // workgroups arrived per XCD, unit claims (after the head claims) per (team, wave)
-constexpr int kSchedWords = 3 * kMaxGrid * kMaxGrid + kMaxGrid + 1 + kMaxGrid;
+constexpr int kSchedGate = 3 * kMaxGrid * kMaxGrid + kMaxGrid + 1 + kMaxGrid; // nonzero: the epoch does nothing
+constexpr int kSchedWords = kSchedGate + 1;
 
 struct DebugSink;
 
@@ -119,9 +120,11 @@ hipError_t init_f16(void* A, int64_t rows, int k, int KP, uint64_t stream, doubl
 
 // Implemented in mfsgd_aux.hip (type-independent kernels).
 hipError_t rmse_final(const double* partial, int64_t ntest, double* out, hipStream_t st);
-hipError_t check_indices(const Sample* S, int64_t nnz, int64_t m, int64_t n, int* bad, hipStream_t st);
-// zero the column tickets and the kSchedWords claim counters (a fill kernel, safe under graph capture)
-hipError_t reset_tickets(uint32_t* tickets, uint32_t* sched, hipStream_t st);
+// raises *bad, and *too if given, on an index out of range
+hipError_t check_indices(const Sample* S, int64_t nnz, int64_t m, int64_t n, int* bad, int* too, hipStream_t st);
+// zero the column tickets and the kSchedWords claim counters (a fill kernel, safe under graph capture); if `one` is
+// given, one[0], one[1] = 0, nnz: the block starts of a one-block grid
+hipError_t reset_tickets(uint32_t* tickets, uint32_t* sched, int64_t* one, int64_t nnz, hipStream_t st);
 hipError_t block_priority(const int64_t* bstart, int s, uint64_t sigma_c, uint64_t sigma_o, uint32_t* prio,
                           hipStream_t st);
 // XCC id of each of `n` one-wavefront workgroups (to learn the dispatch layout)

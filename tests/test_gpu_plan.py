@@ -93,6 +93,63 @@ def test_one_block_epoch_refuses_bad_indices(M):
     assert e.value.code == M.EINVAL
 
 
+@pytest.mark.parametrize("workers", [0, 1])
+@pytest.mark.parametrize("k, partition, column, index", [(16, 2, 0, -1), (64, 4, 1, 97), (128, 4, 0, 1 << 30)])
+def test_one_block_epoch_refuses_bad_indices_in_a_rewritten_array(M, k, partition, column, index, workers):
+    """An array rewritten in place is checked again: an epoch on a bad index
+    does nothing and the next call that waits says so; the call after it, and
+    the next epoch, are good again."""
+    import torch
+    m, n, nnz = 4001, 97, 5003
+    M.reset_options()
+    M.set_option("partition", partition)
+    M.set_option("workers", workers)
+    M.init(m, n, k, 1)
+    d = M.samples_to_device(samples(m, n, nnz, 1, skew=True))
+    M.epoch(d, 0.01, 0.0, 0.0, "hogwild")
+    assert M.get_option("hogwild_form") == 4
+    before = M.get_factors(m, n, k)
+    for at in (0, 2600, nnz - 1):
+        good = int(d[at, column])
+        d[at, column] = index
+        M.epoch(d, 0.01, 0.0, 0.0, "hogwild")
+        with pytest.raises(M.MfsgdError) as e:
+            M.rmse(d[:0])
+        assert e.value.code == M.EINVAL
+        after = M.get_factors(m, n, k)
+        assert torch.equal(before[0], after[0]) and torch.equal(before[1], after[1])
+        d[at, column] = good
+    M.epoch(d, 0.01, 0.0, 0.0, "hogwild")
+    assert not torch.equal(before[0], M.get_factors(m, n, k)[0])
+
+
+def test_captured_one_block_epoch_keeps_its_own_length(M):
+    """A captured one-XCD epoch is replayed after an epoch on a longer array:
+    it trains on its own array, all of it and nothing past it."""
+    import torch
+    m, n, k, short, long = 301, 103, 40, 4999, 20_011
+    M.reset_options()
+    M.set_option("partition", 4)
+    M.set_option("workers", 1)
+    M.init(m, n, k, 3)
+    S = samples(m, n, short, 1, skew=False)
+    a, b = M.samples_to_device(S), M.samples_to_device(samples(m, n, long, 2, skew=False))
+    M.epoch(a, 0.01, 0.05, 0.05, "hogwild")
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        M.epoch(a, 0.01, 0.05, 0.05, "hogwild")
+    P, Q = oracle.init_factors(m, n, k, 3, np.float32)
+    start = [torch.from_numpy(x.copy()) for x in (P, Q)]
+    oracle.epoch_serial(P, Q, S, 0.01, 0.05, 0.05)
+    for _ in range(3):
+        M.epoch(b, 0.01, 0.05, 0.05, "hogwild")
+        M.set_factors(*start)
+        graph.replay()
+        torch.cuda.synchronize()
+        for got, want in zip(M.get_factors(m, n, k), (P, Q)):
+            assert float(np.abs(got.cpu().numpy() - want).max()) <= 1e-4
+
+
 @pytest.mark.parametrize("share, form", [(1 / 60, 4), (1 / 70, 0)])
 def test_automatic_form_on_large_arrays(M, share, form):
     """The largest row's share decides the automatic form (1/64); on arrays
