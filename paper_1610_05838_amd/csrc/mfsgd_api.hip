@@ -1443,8 +1443,6 @@ int epoch_impl(const mfsgd_sample* samples, int64_t nnz, float lr, float lp, flo
             want = g_opt.team_waves;
         a.scheme = kSchemeWavefront;
         a.S = pl->whole ? (const Sample*)samples : pl->Sp;
-        a.last_u = (uint32_t)(c.m - 1);
-        a.last_v = (uint32_t)(c.n - 1);
         a.bstart = pl->whole ? c.one : pl->bstart;
         a.s = s;
         // Pooled wavefronts that claim two batches at a time and run one per

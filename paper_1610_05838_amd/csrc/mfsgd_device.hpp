@@ -453,13 +453,23 @@ __device__ __forceinline__ void add_row(T* p, const float (&d)[E])
     }
 }
 
+// EARLY: a chunk's records are waited for where they are requested, once per
+// 64 samples, instead of where the chunk begins.  Requested ahead, they are
+// still in flight (for the compiler) when the in-chunk loop is entered, and at
+// the loop's head it then waits for everything outstanding, the previous
+// sample's stores included, before every sample.  With one sample in flight
+// that wait is exposed: batch-Hogwild! in one XCD, 20 M Netflix-shaped samples,
+// ms per epoch without and with EARLY: k = 32 15.6 and 10.8, k = 64 12.9 and
+// 10.7, k = 128 binary16 13.5 and 11.6, binary32 18.8 and 18.6 (memory bound).
+// With two in flight it is hidden and the early wait costs instead
+// (deterministic schedule, 1 M samples, s = 32: 8.5 and 8.8 ms), so the callers
+// ask for it at D = 1.
 template <int KP, typename T, int D, bool DBG, bool SKIP = false, bool BUF = false, int COH = kCohOff,
-          bool ATOM = false>
+          bool ATOM = false, bool EARLY = false>
 __device__ __forceinline__ void run_worker(const Sample* __restrict__ S, int64_t nnz, int64_t W, int64_t worker,
                                            int f, T* __restrict__ P, T* __restrict__ Q, float lr, float lp,
                                            float lq, const DebugSink dbg, const CacheSync sync = CacheSync{0, false, false},
-                                           T* sink = nullptr, const Coherence coh = Coherence{nullptr, nullptr, false, false},
-                                           uint32_t last_u = ~0u, uint32_t last_v = ~0u)
+                                           T* sink = nullptr, const Coherence coh = Coherence{nullptr, nullptr, false, false})
 {
     constexpr int E = Geo<KP>::E;
     static_assert(!BUF || (!SKIP && sizeof(T) * E == 4), "buffer rows: one dword per lane, no store redirection");
@@ -494,9 +504,11 @@ __device__ __forceinline__ void run_worker(const Sample* __restrict__ S, int64_t
         cnt = rem <= 0 ? 0 : (rem >= 64 ? 64 : (int)rem);
         const int64_t i = s0 + (lane < cnt ? lane : 0);
         const Sample* sp = S + (cnt > 0 ? i : 0);
-        cu = (int)min((uint32_t)__builtin_nontemporal_load(&sp->u), last_u);
-        cv = (int)min((uint32_t)__builtin_nontemporal_load(&sp->v), last_v);
+        cu = __builtin_nontemporal_load(&sp->u);
+        cv = __builtin_nontemporal_load(&sp->v);
         cr = __builtin_nontemporal_load(&sp->r);
+        if constexpr (EARLY)
+            asm volatile("" : "+v"(cu), "+v"(cv));
     };
 
     if (nnz <= 0 || worker * (int64_t)f >= nnz)
@@ -806,14 +818,13 @@ __device__ __forceinline__ void run_worker(const Sample* __restrict__ S, int64_t
 // SKIP (block-scheduled epochs at rows wider than 32 values): as in
 // run_worker, a row that one of the half's next D-1 samples updates again is
 // stored to the half's private sink row instead (sink: 4 rows per wavefront,
-// P and Q of lanes 0-31, then of lanes 32-63).
-template <int KP, typename T, int D, bool DBG, bool BUF = false, bool SKIP = false>
+// P and Q of lanes 0-31, then of lanes 32-63).  EARLY: as in run_worker.
+template <int KP, typename T, int D, bool DBG, bool BUF = false, bool SKIP = false, bool EARLY = false>
 __device__ __forceinline__ void run_worker_half(const Sample* __restrict__ S, int64_t nnz, int64_t W, int64_t wave,
                                                 int f, T* __restrict__ P, T* __restrict__ Q, float lr, float lp,
                                                 float lq, const DebugSink dbg,
                                                 const CacheSync sync = CacheSync{0, false, false},
-                                                T* __restrict__ sink = nullptr, uint32_t last_u = ~0u,
-                                                uint32_t last_v = ~0u)
+                                                T* __restrict__ sink = nullptr)
 {
     constexpr int H = 32;      // positions per chunk and half; lanes per half
     constexpr int E = KP / H;  // values per lane
@@ -857,9 +868,11 @@ __device__ __forceinline__ void run_worker_half(const Sample* __restrict__ S, in
         const int mine = hi ? c1 : c0;
         const int64_t i = s0 + (hi ? f : 0) + (hl < mine ? hl : 0);
         const Sample* sp = S + (mine > 0 ? i : 0);
-        cu = (int)min((uint32_t)__builtin_nontemporal_load(&sp->u), last_u);
-        cv = (int)min((uint32_t)__builtin_nontemporal_load(&sp->v), last_v);
+        cu = __builtin_nontemporal_load(&sp->u);
+        cv = __builtin_nontemporal_load(&sp->v);
         cr = __builtin_nontemporal_load(&sp->r);
+        if constexpr (EARLY)
+            asm volatile("" : "+v"(cu), "+v"(cv));
     };
 
     if (nnz <= 0 || w0 >= W || w0 * (int64_t)f >= nnz)

@@ -110,11 +110,6 @@ __global__ __launch_bounds__(kHogwildBlock) void k_hogwild_half(const Sample* __
 // the block of wave w+1 must be claimed only after the block of wave w was
 // completed; the host checks that from the stamps.
 //
-// last_u, last_v: the largest row of P and Q.  The one-block grid (s = 1) reads
-// the caller's array itself, whose indices were checked when the array was
-// first seen; they are held to these bounds again as each 64 records are
-// read, so that an array rewritten since cannot reach outside the factors.
-//
 // HALF (rows of at most 16 bytes per half-wavefront lane): a wavefront claims
 // two consecutive batches of the block at once and runs them as two workers,
 // one per half (run_worker_half); the block's finished count advances by the
@@ -130,7 +125,7 @@ __global__ __launch_bounds__(256) void k_blocked(const Sample* __restrict__ Sp, 
                                                  T* __restrict__ Q, float lr, float lp, float lq, int f,
                                                  uint32_t* tickets, uint32_t* sched, uint32_t spin_limit, int* err,
                                                  DebugSink dbg, int32_t* trace, T* __restrict__ sink,
-                                                 Coherence coh, uint32_t last_u, uint32_t last_v)
+                                                 Coherence coh)
 {
     static_assert(!HALF || (KP == 32 ? !SKIP : kHalfRows<KP, T>),
                   "half-wavefront workers: at most 16 bytes of a row per lane; at 32 values no store redirection");
@@ -317,15 +312,13 @@ __global__ __launch_bounds__(256) void k_blocked(const Sample* __restrict__ Sp, 
         else if (blk.visits) // the caller's own array as one block
             blk.visits += b0;
         if constexpr (HALF && KP == 32)
-            run_worker_half<KP, T, D, DBG>(Sp + b0, cnt, 2, 0, f, P, Q, lr, lp, lq, blk, CacheSync{0, false, false},
-                                           nullptr, last_u, last_v);
+            run_worker_half<KP, T, D, DBG, false, false, D == 1>(Sp + b0, cnt, 2, 0, f, P, Q, lr, lp, lq, blk);
         else if constexpr (HALF)
-            run_worker_half<KP, T, D, DBG, false, SKIP>(Sp + b0, cnt, 2, 0, f, P, Q, lr, lp, lq, blk,
-                                                        CacheSync{0, false, false}, my_sink, last_u, last_v);
+            run_worker_half<KP, T, D, DBG, false, SKIP, D == 1>(Sp + b0, cnt, 2, 0, f, P, Q, lr, lp, lq, blk,
+                                                                CacheSync{0, false, false}, my_sink);
         else
-            run_worker<KP, T, D, DBG, SKIP, false, kCohOff, ATOM>(Sp + b0, cnt, 1, 0, f, P, Q, lr, lp, lq, blk,
-                                                                 CacheSync{0, false, false}, my_sink, coh, last_u,
-                                                                 last_v);
+            run_worker<KP, T, D, DBG, SKIP, false, kCohOff, ATOM, D == 1>(
+                Sp + b0, cnt, 1, 0, f, P, Q, lr, lp, lq, blk, CacheSync{0, false, false}, my_sink, coh);
         // this wavefront's stores have reached the XCD's L2 before it counts
         // the batches as finished
         __builtin_amdgcn_s_waitcnt(0);
@@ -727,7 +720,7 @@ static hipError_t launch_epoch_d(const EpochLaunch& a, hipStream_t st)
                 hipLaunchKernelGGL((k_blocked<KP, T, D, DBG, false, true>), dim3((unsigned)a.grid),
                                    dim3(64 * a.wg_waves), 0, st, a.S, a.bstart, a.s, a.xslots, a.tmap, a.xteams, a.nx, a.pool, a.prio,
                                    a.free_run, a.sigma_c, a.sigma_o, a.tail, P, Q, a.lr, a.lp, a.lq, a.f, a.tickets, a.sched,
-                                   a.spin_limit, a.err, dbg, a.trace_wave, (T*)nullptr, acoh, a.last_u, a.last_v);
+                                   a.spin_limit, a.err, dbg, a.trace_wave, (T*)nullptr, acoh);
                 return hipGetLastError();
             }
         }
@@ -740,12 +733,12 @@ static hipError_t launch_epoch_d(const EpochLaunch& a, hipStream_t st)
                     hipLaunchKernelGGL((k_blocked<KP, T, D, false, true, true>), dim3((unsigned)a.grid),
                                        dim3(64 * a.wg_waves), 0, st, a.S, a.bstart, a.s, a.xslots, a.tmap, a.xteams, a.nx,
                                        a.pool, a.prio, a.free_run, a.sigma_c, a.sigma_o, a.tail, P, Q, a.lr, a.lp, a.lq, a.f,
-                                       a.tickets, a.sched, a.spin_limit, a.err, dbg, a.trace_wave, (T*)a.sink, acoh, a.last_u, a.last_v);
+                                       a.tickets, a.sched, a.spin_limit, a.err, dbg, a.trace_wave, (T*)a.sink, acoh);
                 else
                     hipLaunchKernelGGL((k_blocked<KP, T, D, DBG, false, true>), dim3((unsigned)a.grid),
                                        dim3(64 * a.wg_waves), 0, st, a.S, a.bstart, a.s, a.xslots, a.tmap, a.xteams, a.nx,
                                        a.pool, a.prio, a.free_run, a.sigma_c, a.sigma_o, a.tail, P, Q, a.lr, a.lp, a.lq, a.f,
-                                       a.tickets, a.sched, a.spin_limit, a.err, dbg, a.trace_wave, (T*)nullptr, acoh, a.last_u, a.last_v);
+                                       a.tickets, a.sched, a.spin_limit, a.err, dbg, a.trace_wave, (T*)nullptr, acoh);
                 return hipGetLastError();
             }
         }
@@ -754,7 +747,7 @@ static hipError_t launch_epoch_d(const EpochLaunch& a, hipStream_t st)
                 hipLaunchKernelGGL((k_blocked<KP, T, 1, DBG, false, false, true>), dim3((unsigned)a.grid),
                                    dim3(64 * a.wg_waves), 0, st, a.S, a.bstart, a.s, a.xslots, a.tmap, a.xteams, a.nx, a.pool, a.prio,
                                    a.free_run, a.sigma_c, a.sigma_o, a.tail, P, Q, a.lr, a.lp, a.lq, a.f, a.tickets, a.sched,
-                                   a.spin_limit, a.err, dbg, a.trace_wave, (T*)nullptr, acoh, a.last_u, a.last_v);
+                                   a.spin_limit, a.err, dbg, a.trace_wave, (T*)nullptr, acoh);
                 return hipGetLastError();
             }
         }
@@ -765,12 +758,12 @@ static hipError_t launch_epoch_d(const EpochLaunch& a, hipStream_t st)
             hipLaunchKernelGGL((k_blocked<KP, T, D, false, true>), dim3((unsigned)a.grid), dim3(64 * a.wg_waves), 0,
                                st, a.S, a.bstart, a.s, a.xslots, a.tmap, a.xteams, a.nx, a.pool, a.prio, a.free_run, a.sigma_c, a.sigma_o, a.tail, P, Q,
                                a.lr, a.lp, a.lq, a.f, a.tickets, a.sched, a.spin_limit, a.err, dbg, a.trace_wave,
-                               (T*)a.sink, acoh, a.last_u, a.last_v);
+                               (T*)a.sink, acoh);
         else
             hipLaunchKernelGGL((k_blocked<KP, T, D, DBG, false>), dim3((unsigned)a.grid), dim3(64 * a.wg_waves), 0,
                                st, a.S, a.bstart, a.s, a.xslots, a.tmap, a.xteams, a.nx, a.pool, a.prio, a.free_run, a.sigma_c, a.sigma_o, a.tail, P, Q,
                                a.lr, a.lp, a.lq, a.f, a.tickets, a.sched, a.spin_limit, a.err, dbg, a.trace_wave,
-                               (T*)nullptr, acoh, a.last_u, a.last_v);
+                               (T*)nullptr, acoh);
     }
     return hipGetLastError();
 }

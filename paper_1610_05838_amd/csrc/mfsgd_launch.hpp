@@ -43,7 +43,6 @@ struct EpochLaunch {
     const uint32_t* hot_p;            // hot-row bits of P (nullptr: none)
     const uint32_t* hot_q;            // hot-row bits of Q
     // block-scheduled epochs
-    uint32_t last_u, last_v; // m - 1 and n - 1
     const int64_t* bstart;
     int s;           // grid side
     int grid;        // workgroups launched
