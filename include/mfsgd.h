@@ -328,7 +328,10 @@ int mfsgd_plan(const mfsgd_sample* samples, int64_t nnz, int32_t s, void* stream
  * since are trained on; the one-XCD form's first epoch checks the indices
  * synchronously (EINVAL), every later one on the stream: an index out of range
  * then makes that epoch do nothing, and the next call that synchronises
- * returns EINVAL.
+ * returns EINVAL.  What was derived from the array before (those copies, the
+ * automatic form's per-row counts, "hot_log2" rows) is kept until another
+ * array takes its place or mfsgd_check_samples is called on the array: a
+ * caller that reuses a buffer for new ratings calls it on each filling.
  * EINVAL: nnz < 0, NULL samples with nnz > 0, unknown scheme, non-finite lr
  * or lambda, (planning) an index out of range, or nnz >= 2^32 for
  * MFSGD_GLOBAL_TABLE.  ESTATE: no init, or a
@@ -387,7 +390,9 @@ int mfsgd_rmse(const mfsgd_sample* test, int64_t ntest, double* rmse_out, void* 
 int mfsgd_rmse_noalloc(const mfsgd_sample* test, int64_t ntest, double* rmse_dev, void* stream);
 
 /* Check that every sample index is in range.  Synchronises `stream`.
- * EINVAL if any is not. */
+ * EINVAL if any is not.  Drops what earlier epochs derived from the array or
+ * from one that overlaps it (see mfsgd_epoch), so the next epoch on it starts
+ * from the ratings it now holds; the plan of mfsgd_plan stays. */
 int mfsgd_check_samples(const mfsgd_sample* samples, int64_t nnz, void* stream);
 
 /* Wait for `stream` and report a device-side error of earlier epochs

@@ -1093,6 +1093,21 @@ int plan_impl(const mfsgd_sample* samples, int64_t nnz, int32_t s, hipStream_t s
     return build_plan(g.wf, samples, nnz, s, balanced_grid(s), (g_opt.debug & 1) != 0, st);
 }
 
+// Drop what earlier epochs derived from arrays that share memory with this one
+// (the caller's plan is the caller's to renew).  The buffers stay.
+void forget_samples(const mfsgd_sample* samples, int64_t nnz)
+{
+    auto drop = [&](const mfsgd_sample*& src, int64_t n) {
+        const uintptr_t a = (uintptr_t)samples, b = (uintptr_t)src;
+        if (src && a < b + (uintptr_t)n * sizeof(mfsgd_sample) && b < a + (uintptr_t)nnz * sizeof(mfsgd_sample))
+            src = nullptr;
+    };
+    drop(g.stats.src, g.stats.nnz);
+    drop(g.hot.src, g.hot.nnz);
+    drop(g.hw.src, g.hw.nnz);
+    drop(g.gt.src, g.gt.nnz);
+}
+
 int check_impl(const mfsgd_sample* samples, int64_t nnz, hipStream_t st)
 {
     if (!g.inited)
@@ -1101,6 +1116,7 @@ int check_impl(const mfsgd_sample* samples, int64_t nnz, hipStream_t st)
         return fail(MFSGD_EINVAL, "bad sample array");
     if (nnz == 0)
         return MFSGD_OK;
+    forget_samples(samples, nnz);
     HIPCHK(hipMemsetAsync(g.bad, 0, sizeof(int), st));
     HIPCHK(check_indices((const Sample*)samples, nnz, g.m, g.n, g.bad, nullptr, st));
     HIPCHK(hipMemcpyAsync(g.hflag, g.bad, sizeof(int), hipMemcpyDeviceToHost, st));

@@ -123,6 +123,49 @@ def test_one_block_epoch_refuses_bad_indices_in_a_rewritten_array(M, k, partitio
     assert not torch.equal(before[0], M.get_factors(m, n, k)[0])
 
 
+def test_checking_a_rewritten_array_renews_what_was_derived_from_it(M):
+    """mfsgd_check_samples on a refilled buffer: the automatic form is chosen
+    for the new ratings, and the forms that keep a copy train on them."""
+    import torch
+    m, n, k, nnz = 4000, 2000, 128, 40_000
+    S = samples(m, n, nnz, 1, skew=False)
+    S["u"] = S["u"] % (m // 2)  # the first half of the users
+    hot = S.copy()
+    hot["u"] += m // 2  # the second half, and one item with half of the samples
+    hot["v"][::2] = 7
+    first, second = M.samples_to_device(S), M.samples_to_device(hot)
+    other = first.clone()
+
+    def moved(P, was):  # which halves of the users the epoch updated
+        d = (P != was).any(1)
+        return bool(d[:m // 2].any()), bool(d[m // 2:].any())
+
+    for opts, scheme in ((dict(partition=2), "hogwild"), (dict(partition=1), "hogwild"),
+                         (dict(table_grid=16), "table"), (dict(partition=0, coherent=1, hot_log2=4), "hogwild")):
+        M.reset_options()
+        for key, val in opts.items():
+            M.set_option(key, val)
+        M.init(m, n, k, 1)
+        buf = first.clone()
+        keeps = opts.get("partition") == 1 or scheme == "table"
+
+        def epoch():
+            was = M.get_factors(m, n, k)[0]
+            M.epoch(buf, 0.001, 0.01, 0.01, scheme)
+            return moved(M.get_factors(m, n, k)[0], was)
+
+        assert epoch() == (True, False)
+        form = M.get_option("hogwild_form")
+        buf.copy_(second)
+        M.check_samples(other)  # another array: nothing of this one's is dropped
+        assert epoch() == ((True, False) if keeps else (False, True))
+        assert M.get_option("hogwild_form") == form
+        M.check_samples(buf[100:101])  # a part of it
+        assert epoch() == (False, True)
+        if opts.get("partition") == 2:
+            assert (form, M.get_option("hogwild_form")) == (0, 4)
+
+
 def test_captured_one_block_epoch_keeps_its_own_length(M):
     """A captured one-XCD epoch is replayed after an epoch on a longer array:
     it trains on its own array, all of it and nothing past it."""
