@@ -229,7 +229,10 @@ enum { MFSGD_FP32 = 0, MFSGD_FP16 = 1 };
  *                  half of the samples of its row or column block (many
  *                  wavefronts then update one row at once), except in
  *                  partitioned batch-Hogwild! at k <= 32 with "half_waves"
- *                  on.  Epochs with debug output never skip.
+ *                  on.  For equal index ranges and more than 2^20 samples
+ *                  that share is taken from 2^20 of them, spread over the
+ *                  array, and blocks holding fewer than 64 of those do not
+ *                  count.  Epochs with debug output never skip.
  *   "stage_samples" most samples per chunk of mfsgd_epoch_staged (default
  *                  2^25, 402 MB per buffer; three device buffers, and three
  *                  pinned host buffers for pageable arrays).  Chunks are
@@ -281,7 +284,8 @@ enum { MFSGD_FP32 = 0, MFSGD_FP16 = 1 };
  * wavefront for this model), "blocked_pairs" (whether the last
  * block-scheduled epoch, wavefront-update or block-scheduled
  * batch-Hogwild!, had each wavefront claim two batches and run one per half;
- * -1 before one),
+ * -1 before one), "blocked_skips" (whether that epoch redirected stores, see
+ * "skip_stores"; -1 before one),
  * "table_blocks" (non-empty blocks of the last global-table plan, 0 before one),
  * "blocked_per_cu" (workgroups per CU the occupancy query reports for the
  * block-scheduled kernel with one batch per claim; the two-batch variant

@@ -161,6 +161,7 @@ struct Context {
     int last_form = -1;     // form of the last batch-Hogwild! epoch (values of option "partition"), -1 before one
     int last_atomic = 0;    // whether it added its updates atomically
     int last_pairs = -1;    // whether the last block-scheduled epoch claimed two batches per wavefront, -1 before one
+    int last_skips = -1;    // whether it redirected stores (skip_stores), -1 before one
     // planner scratch
     int64_t* counts = nullptr;
     int64_t counts_cap = 0;
@@ -535,7 +536,7 @@ int get_option_impl(const char* key, int64_t* value)
                     !std::strcmp(key, "teams_grid") || !std::strcmp(key, "table_blocks") ||
                     !std::strcmp(key, "half_workers") || !std::strcmp(key, "hogwild_form") ||
                     !std::strcmp(key, "hogwild_atomic") || !std::strcmp(key, "xcd_round_robin") ||
-                    !std::strcmp(key, "blocked_pairs");
+                    !std::strcmp(key, "blocked_pairs") || !std::strcmp(key, "blocked_skips");
     if (!ro)
         return fail(MFSGD_EINVAL, std::string("unknown option '") + key + "'");
     if (!g.inited)
@@ -558,6 +559,8 @@ int get_option_impl(const char* key, int64_t* value)
         *value = g.last_atomic;
     else if (!std::strcmp(key, "blocked_pairs"))
         *value = g.last_pairs;
+    else if (!std::strcmp(key, "blocked_skips"))
+        *value = g.last_skips;
     else if (!std::strcmp(key, "teams_grid"))
         *value = g.lay_plan ? g.lay_grid : 0;
     else if (!std::strcmp(key, "table_blocks"))
@@ -613,6 +616,7 @@ int init_impl(int64_t m, int64_t n, int32_t k, uint64_t seed)
     c.last_form = -1;
     c.last_atomic = 0;
     c.last_pairs = -1;
+    c.last_skips = -1;
     c.stats = RowStats();
     HIPCHK(hipGetDevice(&c.device));
     if (c.device >= 0 && c.device < kMaxDevices && !g_rmse_scratch[c.device]) {
@@ -820,9 +824,14 @@ int build_hot(const mfsgd_sample* samples, int64_t nnz, int log2, hipStream_t st
 }
 
 // Samples whose indices are counted for the hot-row and hot-column measures of
-// an equal-range plan: enough that each of 64 blocks holds about 16,000 of
-// them, a share known to 1 %.
+// an equal-range plan of more samples: evenly filled, each of 64 blocks holds
+// about 16,000 of them, a share known to 1 %.  A block with fewer than
+// kPlanSupport of them is left out: its shares say nothing (the one pick of a
+// nearly empty block is all of it), and a block with 64 of 2^20 samples cannot
+// bound an epoch, whatever its rows.  With 64, a share of 0.3 is taken for more
+// than 0.5 with probability 3e-4.
 constexpr int64_t kPlanPicks = int64_t(1) << 20;
+constexpr unsigned long long kPlanSupport = 64;
 
 int build_plan(Plan& pl, const mfsgd_sample* samples, int64_t nnz, int s, bool balanced, bool keep_orig,
                hipStream_t st)
@@ -852,7 +861,8 @@ int build_plan(Plan& pl, const mfsgd_sample* samples, int64_t nnz, int s, bool b
     if (!c.tops)
         CHK(dalloc((void**)&c.tops, sizeof(unsigned long long) * 4 * kMaxGrid, "block tops"));
     HIPCHK(hipMemsetAsync(c.deg, 0, sizeof(unsigned long long) * (size_t)(c.m + c.n), st));
-    HIPCHK(plan_degrees(S, nnz, balanced ? nnz : std::min(nnz, kPlanPicks), c.m, c.n, c.deg, c.deg + c.m, c.bad, st));
+    const int64_t picks = balanced ? nnz : std::min(nnz, kPlanPicks);
+    HIPCHK(plan_degrees(S, nnz, picks, c.m, c.n, c.deg, c.deg + c.m, c.bad, st));
     std::vector<int64_t> cut(2 * (kMaxGrid + 1));
     int64_t* ccut = cut.data() + kMaxGrid + 1;
     if (balanced) {
@@ -890,9 +900,10 @@ int build_plan(Plan& pl, const mfsgd_sample* samples, int64_t nnz, int s, bool b
         return bad_index_error();
     // largest share of one row block's (column block's) samples that a single
     // user (item) holds
+    const unsigned long long support = picks < nnz ? kPlanSupport : 1;
     pl.hot_row = pl.hot_col = 0.0;
     for (int j = 0; j < 2 * s; ++j)
-        if (tops[2 * (size_t)j] > 0) {
+        if (tops[2 * (size_t)j] >= support) {
             double& h = j < s ? pl.hot_row : pl.hot_col;
             h = std::max(h, (double)tops[2 * (size_t)j + 1] / (double)tops[2 * (size_t)j]);
         }
@@ -1543,6 +1554,7 @@ int epoch_impl(const mfsgd_sample* samples, int64_t nnz, float lr, float lp, flo
                 HIPCHK(epoch_f32(a, st));
         }
         c.last_pairs = a.half ? 1 : 0;
+        c.last_skips = a.sink && !a.visits && a.scheme != kSchemeWaveLaunch ? 1 : 0;
     }
     if (hog) {
         c.last_form = form;

@@ -55,6 +55,27 @@ def test_plan_equals_the_oracles_bucketing(M, s, balance):
         assert np.array_equal(M.debug_plan_order(nnz).cpu().numpy(), order), (m, n, nnz)
 
 
+@pytest.mark.parametrize("nnz, hot, want", [(3_000_000, 0.0, 0), (3_000_000, 0.6, 1), (1 << 20, 0.0, 0),
+                                            ((1 << 20) + 1, 0.6, 1), (1 << 20, 0.6, 1)])
+def test_nearly_empty_blocks_do_not_switch_the_skipped_stores_on(M, nnz, hot, want):
+    """All but 63 x 3 of the samples lie in the first of 64 row blocks; the
+    three of every other block belong to three users.  Stores are skipped only
+    where one user holds most of the first block."""
+    m, n, s = 64_000, 6400, 64
+    M.reset_options()
+    M.init(m, n, 128, 1)
+    S = samples(m, n, nnz, 3, skew=False)
+    S["u"] %= m // s
+    S["u"][:int(nnz * hot)] = 5
+    at = np.random.default_rng(4).choice(nnz, 3 * (s - 1), replace=False)
+    S["u"][at] = m // s + np.arange(3 * (s - 1)) * (m // s) // 3
+    assert np.all(np.bincount(S["u"].astype(np.int64) * s // m, minlength=s)[1:] == 3)
+    d = M.samples_to_device(S)
+    M.plan(d, s)
+    M.epoch(d, 0.0, 0.0, 0.0, "wavefront")
+    assert M.get_option("blocked_skips") == want
+
+
 @pytest.mark.parametrize("dtype", [0, 1])
 @pytest.mark.parametrize("nnz", [1, 63, 64, 65, 255, 257, 5003])
 def test_one_block_epoch_reads_the_callers_array(M, nnz, dtype):
