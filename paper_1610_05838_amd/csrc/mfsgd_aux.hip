@@ -571,6 +571,16 @@ __global__ __launch_bounds__(1024) void k_plan_scan_blocks(const int64_t* __rest
         bstart[nb] = part[1023];
 }
 
+// Orders the LDS accesses of a wavefront's lanes with each other.  The hardware
+// completes them in order, so this costs no instruction: it keeps the compiler
+// from moving one lane's read past another lane's write.
+__device__ __forceinline__ void wave_order()
+{
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+}
+
 // One workgroup of NW wavefronts per chunk, in tiles of NW * kPlanRounds * 64
 // samples, wavefront w taking the w-th part of the tile.
 //   * Within 64 samples the ones of one block find each other with one ballot
@@ -648,13 +658,12 @@ __global__ __launch_bounds__(64 * NW) void k_plan_scatter(const Sample* __restri
             }
             const int rank = (int)__builtin_amdgcn_mbcnt_hi(hi32, __builtin_amdgcn_mbcnt_lo(lo32, 0u));
             bin[r] = valid ? b : -1;
-            at[r] = 0;
-            if (valid) {
-                const int have = cnt[w][b];
-                at[r] = have + rank;
-                if (rank == 0) // after every lane's read: a wavefront's LDS accesses complete in order
-                    cnt[w][b] = (uint16_t)(have + __popc(lo32) + __popc(hi32));
-            }
+            const int have = cnt[w][b];
+            at[r] = have + rank;
+            wave_order(); // every lane has read the count ...
+            if (valid && rank == 0)
+                cnt[w][b] = (uint16_t)(have + __popc(lo32) + __popc(hi32));
+            wave_order(); // ... before the block's first lane moves it on, for the next 64 to read
         }
         __syncthreads();
         uint32_t total[kPer];
