@@ -1,7 +1,10 @@
 """The wavefront-update planner against the oracle's stable bucketing: block
 starts and planned positions, bit for bit, at the grid sides where the
-scatter's block-id width changes (4, 8, 16, 32), at sizes around its tiles of
-8192 samples, for both cuts, and for models narrower than the grid."""
+scatter's block-id width changes (4, 8, 16, 32), for both cuts, for models
+narrower than the grid, and at sizes where one of its 512 chunks fills one tile
+of 8192 samples, one more, and several; above 2^32 - 1 samples (another variant
+of the scatter) against the definition of the order itself.  Then the one-block
+grid, which is the caller's array as it stands."""
 import numpy as np
 import pytest
 
@@ -53,6 +56,70 @@ def test_plan_equals_the_oracles_bucketing(M, s, balance):
         got = M.debug_plan_starts(s).cpu().numpy()
         assert np.array_equal(got, start), (m, n, nnz)
         assert np.array_equal(M.debug_plan_order(nnz).cpu().numpy(), order), (m, n, nnz)
+
+
+@pytest.mark.parametrize("s", [4, 8, 16, 32, 64])
+@pytest.mark.parametrize("nnz", [512 * 8192 - 1, 512 * 8192, 512 * 8192 + 1, 512 * 8192 + 512 * 1025, 9_000_011])
+def test_plan_of_several_tiles_per_chunk(M, nnz, s):
+    """Chunks of one full tile, of a tile and one sample, of a tile and a
+    little more than one wavefront's part, of three tiles; one half of the
+    samples in one column block."""
+    m, n = 4001, 1999
+    M.reset_options()
+    M.set_option("balance", 0)
+    M.set_option("debug", 1)
+    M.init(m, n, 8, 1)
+    S = samples(m, n, nnz, s, skew=True)
+    order, start = oracle.block_order(S, m, n, s)
+    M.plan(M.samples_to_device(S), s)
+    assert np.array_equal(M.debug_plan_starts(s).cpu().numpy(), start)
+    assert np.array_equal(M.debug_plan_order(nnz).cpu().numpy(), order)
+
+
+def test_plan_of_more_than_32_bits_of_samples(M):
+    """2^32 + 4097 samples: (block, position) rises strictly along the planned
+    order and the block starts are the counts' sums, which is the stable order
+    and nothing else."""
+    import torch
+    m, n, nnz, step = 70_001, 5003, (1 << 32) + 4097, 1 << 26
+    if torch.cuda.mem_get_info()[0] < 200 << 30:
+        pytest.skip("needs 200 GB of GPU memory")
+    M.reset_options()
+    M.set_option("balance", 0)
+    M.set_option("debug", 1)
+    M.init(m, n, 8, 1)
+    g = torch.Generator(device="cuda").manual_seed(7)
+    S = torch.zeros((nnz, 3), dtype=torch.int32, device="cuda")
+    for at in range(0, nnz, step):
+        b = min(step, nnz - at)
+        S[at:at + b, 0] = torch.randint(0, m, (b,), device="cuda", generator=g, dtype=torch.int32)
+        S[at:at + b, 1] = torch.randint(0, n, (b,), device="cuda", generator=g, dtype=torch.int32)
+    S[::2, 1] = 77
+
+    def blocks(x, s):
+        return (x[:, 0].long() * s // m) * s + x[:, 1].long() * s // n
+
+    for s in (4, 8, 16, 32, 64):
+        M.plan(S, s)
+        count = torch.zeros(s * s, dtype=torch.int64, device="cuda")
+        for at in range(0, nnz, step):
+            count += torch.bincount(blocks(S[at:at + step], s), minlength=s * s)
+        start = M.debug_plan_starts(s)
+        assert int(start[0]) == 0 and torch.equal(start[1:], count.cumsum(0)), s
+        order = M.debug_plan_order(nnz)
+        last = (-1, -1)
+        for at in range(0, nnz, step):
+            o = order[at:at + step]
+            assert int(o.min()) >= 0 and int(o.max()) < nnz, (s, at)
+            b = blocks(S[o], s)
+            rises = (b[1:] > b[:-1]) | ((b[1:] == b[:-1]) & (o[1:] > o[:-1]))
+            assert bool(rises.all()) and (int(b[0]), int(o[0])) > last, (s, at)
+            last = int(b[-1]), int(o[-1])
+        print(f"s = {s}: {nnz} samples in order", flush=True)
+        del order, o, b, rises
+    del S
+    M.finalize()
+    torch.cuda.empty_cache()
 
 
 @pytest.mark.parametrize("nnz, hot, want", [(3_000_000, 0.0, 0), (3_000_000, 0.6, 1), (1 << 20, 0.0, 0),
