@@ -233,10 +233,11 @@ enum { MFSGD_FP32 = 0, MFSGD_FP16 = 1 };
  *                  that share is taken from 2^20 of them, spread over the
  *                  array, and blocks holding fewer than 64 of those do not
  *                  count.  Epochs with debug output never skip.
- *   "stage_samples" most samples per chunk of mfsgd_epoch_staged (default
- *                  2^25, 402 MB per buffer; three device buffers, and three
- *                  pinned host buffers for pageable arrays).  Chunks are
- *                  smaller where one batch per worker and 2^21 samples are.
+ *   "stage_samples" samples per chunk of mfsgd_epoch_staged (rounded down to
+ *                  a multiple of f; 12 bytes each in three device buffers,
+ *                  and in three pinned host buffers for pageable arrays).
+ *                  Until it is set (default 2^25), chunks hold one batch per
+ *                  worker and at least 2^21 samples, at most 2^25.
  *   "wave_launch"  MFSGD_WAVEFRONT_DET only: 1 runs every wave as a kernel
  *                  launch of its own (worker i of wave w updates block
  *                  (i, sigma_i(w)) serially; the launch boundary orders the
@@ -346,8 +347,8 @@ int mfsgd_epoch(const mfsgd_sample* samples, int64_t nnz, float lr, float lambda
 /* One batch-Hogwild! epoch over samples that stay in host memory, for sample
  * arrays larger than the GPU's memory: the out-of-core mode of section 4,
  * where the transfer of the next part of R overlaps the computation on the
- * current one.  The array is cut into chunks of at most "stage_samples"
- * consecutive samples (a multiple of f); chunk i is copied into one of
+ * current one.  The array is cut into chunks of "stage_samples" consecutive
+ * samples (see there for the default); chunk i is copied into one of
  * three library-owned device buffers on a library-owned stream while the
  * kernel of chunk i-1 runs on `stream`, and each chunk is run like
  * MFSGD_BATCH_HOGWILD in one address space (batch b of the chunk to worker

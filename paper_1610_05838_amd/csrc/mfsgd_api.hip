@@ -43,6 +43,7 @@ struct Options {
     int64_t spin_limit = int64_t(1) << 24;
     int64_t skip_stores = 2;
     int64_t stage_samples = int64_t(1) << 25;
+    bool stage_set = false; // "stage_samples" was set: chunks of exactly that many
     int64_t wave_launch = 0;
     int64_t half_waves = 1;
     int64_t table_grid = 256;
@@ -517,6 +518,8 @@ int set_option_impl(const char* key, int64_t value)
         if (!ok)
             return fail(MFSGD_EINVAL, o.what);
         g_opt.*(o.field) = value;
+        if (o.field == &Options::stage_samples)
+            g_opt.stage_set = true;
         return MFSGD_OK;
     }
     return fail(MFSGD_EINVAL, std::string("unknown option '") + key + "'");
@@ -1567,14 +1570,18 @@ int epoch_impl(const mfsgd_sample* samples, int64_t nnz, float lr, float lp, flo
 // ---------------------------------------------------------------------------
 // staged epochs (samples in host memory)
 // ---------------------------------------------------------------------------
-// The sample array is cut into chunks of C consecutive samples, C at most
-// option "stage_samples", a multiple of f.  The first copy and the last kernel
-// overlap with nothing, so chunks are no larger than they need to be: one
-// batch for every worker, and at least kStageLeast samples, below which the
-// cost of a copy and a launch shows (19.8 M binary32 samples at k = 128, pinned:
-// 11.5 / 5.1 / 4.8 / 4.7 / 4.9 / 5.7 ms an epoch in chunks of 2^18 / 2^19 /
-// 2^20 / 2^21 / 2^22 / 2^23, 7.8 ms in one chunk; the copy alone is 4.3 ms at
-// 55 GB/s of PCIe, which bounds it).  Chunk i is copied into
+// The sample array is cut into chunks of C consecutive samples, a multiple of f:
+// option "stage_samples" where it was set.  The first copy and the last kernel
+// overlap with nothing, so by default chunks are no larger than they need to
+// be: one batch for every worker, and at least kStageLeast samples, below which
+// the cost of a copy and a launch shows (19.8 M binary32 samples at k = 128,
+// pinned: 11.5 / 5.1 / 4.8 / 4.7 / 4.9 / 5.7 ms an epoch in chunks of 2^18 /
+// 2^19 / 2^20 / 2^21 / 2^22 / 2^23).  Bound by the copy (57 GB/s of PCIe; on a
+// host whose link gives 30 it takes 7.8 ms and nothing else shows).  Factors in,
+// an epoch, RMSE, factors out, in chunks of 2^25 and so (the copy alone): 19.8 M
+// samples, binary32, k = 128 8.2 and 5.0 ms (4.1); binary16, k = 32 5.2 and 4.6
+// (4.1); pageable 16.2 and 9.8; 60 M 18.3 and 13.8 (12.5); 5 M 2.35 and 1.78
+// (1.05); 3 M, k = 16 0.93 and 0.93 (0.63).  Chunk i is copied into
 // device buffer i mod 3 on the library's copy stream while the caller's
 // stream runs the batch-Hogwild! kernel (one address space) over chunk i-1;
 // events order each copy after the kernel that last read its buffer and
@@ -1669,7 +1676,8 @@ int epoch_staged_impl(const mfsgd_sample* samples, int64_t nnz, float lr, float 
         W = (int64_t)c.cus * per_cu * (half_wave_workers(c.KP, c.dtype) ? 2 : 1);
     }
     a.half = half_wave_workers(c.KP, c.dtype) ? 1 : 0;
-    const int64_t cap = std::min(std::max(kStageLeast, W > kStageMost / f ? kStageMost : W * f), g_opt.stage_samples);
+    const int64_t enough = std::max(kStageLeast, W > kStageMost / f ? kStageMost : W * f);
+    const int64_t cap = g_opt.stage_set ? g_opt.stage_samples : std::min(enough, g_opt.stage_samples);
     const int64_t C = std::max<int64_t>(f, cap / f * f);
     if (dbg & 1) {
         CHK(grow(&c.visits, &c.visits_cap, nnz, "visit counters"));

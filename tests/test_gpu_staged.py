@@ -98,11 +98,33 @@ def test_staged_default_chunks_cover(M, nnz, dtype, k, pinned):
     sample is used exactly once."""
     rng = np.random.default_rng(nnz)
     S = rand_samples(rng, 3000, 2000, nnz)
-    setup(M, 3000, 2000, k, 3, dtype, debug=1)
+    M.reset_options()  # "stage_samples" stays unset
+    M.set_option("dtype", 1 if dtype == np.float16 else 0)
+    M.set_option("debug", 1)
+    M.init(3000, 2000, k, 3)
     H = host(S, True) if pinned else S  # kept until the copies are done
     for _ in range(2):
         M.epoch_staged(H, 0.0001, 0.05, 0.05)
         assert bool((M.debug_visits(nnz) == 1).all())
+
+
+def test_staged_chunks_hold_what_the_option_says(M):
+    """A chunk size that was set is taken as it is, up or down; the default is
+    smaller.  Read from the memory the three device buffers take."""
+    import torch
+    m, n, nnz = 3000, 2000, (1 << 24) + 5
+    H = torch.zeros((nnz, 3), dtype=torch.int32).pin_memory()
+    for chunk, want in ((1 << 24, 1 << 24), (1 << 25, nnz), (3 << 20, 3 << 20), (None, 1 << 21)):
+        M.reset_options()
+        if chunk is not None:
+            M.set_option("stage_samples", chunk)
+        M.init(m, n, 128, 1)
+        torch.cuda.synchronize()
+        before = torch.cuda.mem_get_info()[0]
+        M.epoch_staged(H, 0.0, 0.0, 0.0)
+        torch.cuda.synchronize()
+        taken = before - torch.cuda.mem_get_info()[0]
+        assert abs(taken - 3 * 12 * want) <= 3 * (2 << 20), (chunk, taken)  # allocations are whole 2 MiB pages
 
 
 def test_staged_lr_zero_is_identity(M):
