@@ -329,8 +329,8 @@ int mfsgd_plan(const mfsgd_sample* samples, int64_t nnz, int32_t s, void* stream
  * of range is undefined behaviour there.
  * A sample array is known by its address and length: forms 1 and 3 and the
  * global table keep a copy made on its first epoch and train on that.  The
- * one-XCD form (and form 0) reads the array itself, so ratings written over it
- * since are trained on; the one-XCD form's first epoch checks the indices
+ * one-XCD form (any one-block grid) and form 0 read the array itself, so
+ * ratings written over it since are trained on; the one-XCD form's first epoch checks the indices
  * synchronously (EINVAL), every later one on the stream: an index out of range
  * then makes that epoch do nothing, and the next call that synchronises
  * returns EINVAL.  What was derived from the array before (those copies, the

@@ -754,7 +754,7 @@ int bad_index_error()
 // so the indices that kTopLeast of 2^20 evenly spread samples hold are found
 // first and only those are counted in full, in one pass bound by reading the
 // samples.  A share of kTopShare gives 357 of the picks on average and fewer
-// than 256 with probability 4e-8.
+// than 256 with probability 1e-8.
 constexpr int64_t kTopPicks = int64_t(1) << 20;
 constexpr int64_t kTopLeast = 256;
 constexpr double kTopShare = 3.4e-4;

@@ -454,16 +454,16 @@ __device__ __forceinline__ void add_row(T* p, const float (&d)[E])
 }
 
 // EARLY: a chunk's records are waited for where they are requested, once per
-// 64 samples, instead of where the chunk begins.  Requested ahead, they are
-// still in flight (for the compiler) when the in-chunk loop is entered, and at
-// the loop's head it then waits for everything outstanding, the previous
-// sample's stores included, before every sample.  With one sample in flight
-// that wait is exposed: batch-Hogwild! in one XCD, 20 M Netflix-shaped samples,
-// ms per epoch without and with EARLY: k = 32 15.6 and 10.8, k = 64 12.9 and
-// 10.7, k = 128 binary16 13.5 and 11.6, binary32 18.8 and 18.6 (memory bound).
-// With two in flight it is hidden and the early wait costs instead
-// (deterministic schedule, 1 M samples, s = 32: 8.5 and 8.8 ms), so the callers
-// ask for it at D = 1.
+// 64 samples, instead of where the chunk begins.  Requested ahead, they may
+// (for the compiler) still be in flight when the in-chunk loop is entered, and
+// the wait for them that it puts at the loop's head, s_waitcnt vmcnt(1), waits
+// in every later pass for the previous sample's first store instead.  With one
+// sample in flight that wait is exposed: batch-Hogwild! in one XCD, 20 M
+// Netflix-shaped samples, ms per epoch without and with EARLY: k = 32 15.5 and
+// 10.8, k = 64 12.8 and 10.6, k = 128 binary16 13.4 and 11.4, binary32 18.8 and
+// 18.7 (memory bound).  With two in flight it is hidden and the early wait costs
+// instead (deterministic schedule, 1 M samples, s = 32: 8.4 and 8.8 ms), so the
+// callers ask for it at D = 1.
 template <int KP, typename T, int D, bool DBG, bool SKIP = false, bool BUF = false, int COH = kCohOff,
           bool ATOM = false, bool EARLY = false>
 __device__ __forceinline__ void run_worker(const Sample* __restrict__ S, int64_t nnz, int64_t W, int64_t worker,
