@@ -1132,7 +1132,7 @@ int check_impl(const mfsgd_sample* samples, int64_t nnz, hipStream_t st)
         return MFSGD_OK;
     forget_samples(samples, nnz);
     HIPCHK(hipMemsetAsync(g.bad, 0, sizeof(int), st));
-    HIPCHK(check_indices((const Sample*)samples, nnz, g.m, g.n, g.bad, nullptr, st));
+    HIPCHK(check_indices((const Sample*)samples, nnz, g.m, g.n, g.bad, st));
     HIPCHK(hipMemcpyAsync(g.hflag, g.bad, sizeof(int), hipMemcpyDeviceToHost, st));
     HIPCHK(hipStreamSynchronize(st));
     const int bad = *g.hflag;
@@ -1516,18 +1516,20 @@ int epoch_impl(const mfsgd_sample* samples, int64_t nnz, float lr, float lp, flo
         a.sigma_o = sm64_at(c.seed, kTagWaveOffset + 2ull * (uint64_t)c.epoch);
         if (!(scheme == MFSGD_WAVEFRONT_DET && g_opt.wave_launch))
             HIPCHK(reset_tickets(c.tickets, c.sched, pl->whole ? c.one : nullptr, nnz, st));
-        // The caller's own array is read again by every epoch, so its indices
-        // are checked again before each (on the stream, nothing is waited
-        // for: 0.25 ms before the Netflix shape's 91 ms); a bad one closes
-        // the gate, and the next synchronising call reports it.
-        if (pl->whole && !seen)
-            HIPCHK(check_indices((const Sample*)samples, nnz, c.m, c.n, (int*)c.sched + kSchedGate, c.err + 1, st));
-        a.prio = nullptr;
-        if (a.pool && g_opt.priority) {
-            HIPCHK(block_priority(a.bstart, s, a.sigma_c, a.sigma_o, c.prio, st));
-            a.prio = c.prio;
-            c.prio_s = s;
+        uint32_t* const prio = a.pool && g_opt.priority ? c.prio : nullptr;
+        if (pl->whole && !seen) {
+            // The caller's own array is read again by every epoch, so its
+            // indices are checked again before each (on the stream, nothing is
+            // waited for); a bad one closes the gate, and the next
+            // synchronising call reports it.
+            HIPCHK(check_one_block((const Sample*)samples, nnz, c.m, c.n, (int*)c.sched + kSchedGate, c.err + 1,
+                                   prio, st));
+        } else if (prio) {
+            HIPCHK(block_priority(a.bstart, s, a.sigma_c, a.sigma_o, prio, st));
         }
+        if (prio)
+            c.prio_s = s;
+        a.prio = prio;
         a.tickets = c.tickets;
         a.sched = c.sched;
         a.free_run = hog && form == 3 ? 1 : 0;

@@ -34,7 +34,8 @@ hipError_t rmse_final(const double* partial, int64_t ntest, double* out, hipStre
     return hipGetLastError();
 }
 
-__global__ void k_check(const Sample* __restrict__ S, int64_t nnz, int64_t m, int64_t n, int* bad, int* too)
+__global__ void k_check(const Sample* __restrict__ S, int64_t nnz, int64_t m, int64_t n, int* bad, int* too,
+                        uint32_t* prio)
 {
     int found = 0;
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < nnz; i += (int64_t)gridDim.x * blockDim.x) {
@@ -47,16 +48,27 @@ __global__ void k_check(const Sample* __restrict__ S, int64_t nnz, int64_t m, in
         if (too)
             atomicOr(too, 1);
     }
+    if (prio && blockIdx.x == 0 && threadIdx.x == 0) {
+        const int64_t units = (nnz + 63) / 64;
+        *prio = units > 0xffffffffll ? 0xffffffffu : (uint32_t)units;
+    }
 }
 
-hipError_t check_indices(const Sample* S, int64_t nnz, int64_t m, int64_t n, int* bad, int* too, hipStream_t st)
+hipError_t check_indices(const Sample* S, int64_t nnz, int64_t m, int64_t n, int* bad, hipStream_t st)
 {
     if (nnz <= 0)
         return hipSuccess;
-    int64_t blocks = (nnz + 255) / 256;
-    if (blocks > 8192)
-        blocks = 8192;
-    hipLaunchKernelGGL(k_check, dim3((unsigned)blocks), dim3(256), 0, st, S, nnz, m, n, bad, too);
+    const int64_t blocks = std::min<int64_t>((nnz + 255) / 256, 8192);
+    hipLaunchKernelGGL(k_check, dim3((unsigned)blocks), dim3(256), 0, st, S, nnz, m, n, bad, (int*)nullptr,
+                       (uint32_t*)nullptr);
+    return hipGetLastError();
+}
+
+hipError_t check_one_block(const Sample* S, int64_t nnz, int64_t m, int64_t n, int* gate, int* err, uint32_t* prio,
+                           hipStream_t st)
+{
+    const int64_t blocks = std::max<int64_t>(1, std::min<int64_t>((nnz + 255) / 256, 8192));
+    hipLaunchKernelGGL(k_check, dim3((unsigned)blocks), dim3(256), 0, st, S, nnz, m, n, gate, err, prio);
     return hipGetLastError();
 }
 

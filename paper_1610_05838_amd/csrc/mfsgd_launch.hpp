@@ -119,8 +119,12 @@ hipError_t init_f16(void* A, int64_t rows, int k, int KP, uint64_t stream, doubl
 
 // Implemented in mfsgd_aux.hip (type-independent kernels).
 hipError_t rmse_final(const double* partial, int64_t ntest, double* out, hipStream_t st);
-// raises *bad, and *too if given, on an index out of range
-hipError_t check_indices(const Sample* S, int64_t nnz, int64_t m, int64_t n, int* bad, int* too, hipStream_t st);
+// raises *bad on an index out of range
+hipError_t check_indices(const Sample* S, int64_t nnz, int64_t m, int64_t n, int* bad, hipStream_t st);
+// the same before an epoch on the one-block grid: raises *gate and *err, and writes the block's priority (the launch
+// stands in for block_priority)
+hipError_t check_one_block(const Sample* S, int64_t nnz, int64_t m, int64_t n, int* gate, int* err, uint32_t* prio,
+                           hipStream_t st);
 // zero the column tickets and the kSchedWords claim counters (a fill kernel, safe under graph capture); if `one` is
 // given, one[0], one[1] = 0, nnz: the block starts of a one-block grid
 hipError_t reset_tickets(uint32_t* tickets, uint32_t* sched, int64_t* one, int64_t nnz, hipStream_t st);
