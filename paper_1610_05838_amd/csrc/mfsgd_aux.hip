@@ -34,6 +34,8 @@ hipError_t rmse_final(const double* partial, int64_t ntest, double* out, hipStre
     return hipGetLastError();
 }
 
+// Index check, bound by reading the samples (99 M: 0.17 ms, 6.9 TB/s with part
+// of them in the Infinity Cache).
 __global__ void k_check(const Sample* __restrict__ S, int64_t nnz, int64_t m, int64_t n, int* bad, int* too,
                         uint32_t* prio)
 {
@@ -473,7 +475,8 @@ hipError_t top_degrees(const Sample* S, int64_t nnz, int64_t picks, int64_t leas
 
 // Sixteen wavefronts share a chunk's histogram (up to 16 KB of LDS), two
 // workgroups fill a CU; bound by reading the samples (384 M: 3.84 ms with one
-// wavefront per workgroup and 64-bit divisions, 0.78 ms so, 5.9 TB/s).
+// wavefront per workgroup and 64-bit divisions, 0.78 ms so, 5.9 TB/s; 3.07 G:
+// 6.2 ms).
 __global__ __launch_bounds__(1024) void k_plan_count(const Sample* __restrict__ S, int64_t nnz, int m, int n, int s,
                                                     float su, float sv, const int64_t* __restrict__ rbnd,
                                                     const int64_t* __restrict__ cbnd, int64_t* __restrict__ counts,
@@ -604,12 +607,13 @@ __device__ __forceinline__ void wave_order()
 //   * Per tile the wavefronts' counts are turned into prefix sums, block by
 //     block, which puts the wavefronts' parts in array order.
 // What bounds it is the scattered 12-byte write: at s = 64 a chunk has 4096
-// lines open, and only lines that stay in the 256 MB Infinity Cache until the
-// chunk has filled them reach memory once.  One chunk per CU at a time (256
-// x 4096 lines of 128 B = 134 MB) does that.  384 M samples at s = 64: 51.8 ms
-// taking the distinct blocks one by one, 14.1 ms with the ballots and a chunk
-// per wavefront (2560 chunks in flight, most lines written several times
-// over), 6.2 ms so; 99 M samples at s = 32: 11.9 ms to 1.1 ms.
+// lines open, an XCD's 32 chunks more than its L2 holds, and a line leaves the
+// L2 in pieces, 36 B per sample where 12 would do (WRITE_SIZE; 3.07 G samples:
+// 52.4 ms, 2.8 TB/s past the L2s with the 12 B read).  The fewer chunks are in
+// flight, the longer a line stays, so it is one chunk per CU at a time.  384 M
+// samples at s = 64: 51.8 ms taking the distinct blocks one by one, 14.1 ms with
+// the ballots and a chunk per wavefront (2560 in flight), 6.2 ms so; 99 M
+// samples at s = 32: 11.9 ms to 1.1 ms.
 // OFF: the positions' type, 32 bits where nnz fits them.
 constexpr int kPlanRounds = 8;
 
