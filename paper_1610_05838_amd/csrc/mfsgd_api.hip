@@ -1578,13 +1578,14 @@ int epoch_impl(const mfsgd_sample* samples, int64_t nnz, float lr, float lp, flo
 // be: one batch for every worker, and at least kStageLeast samples, below which
 // the cost of a copy and a launch shows (19.8 M binary32 samples at k = 128,
 // pinned: 11.5 / 5.1 / 4.8 / 4.7 / 4.9 / 5.7 ms an epoch in chunks of 2^18 /
-// 2^19 / 2^20 / 2^21 / 2^22 / 2^23).  Bound by the copy, 57 GB/s of PCIe; about
-// the first 16 copies of a new copy stream, and in some processes all of them,
-// run at 30 GB/s while a kernel runs beside them, and then the chunks gain
-// little (7.9 ms).  Factors in, an epoch, RMSE, factors out, in chunks of 2^25
-// and so (the copy alone): 19.8 M samples, binary32, k = 128 8.2 and 5.0 ms
-// (4.1); binary16, k = 32 5.2 and 4.6 (4.1); pageable 16.2 and 9.8; 60 M 18.3
-// and 13.8 (12.5); 5 M 2.35 and 1.78 (1.05); 3 M, k = 16 0.93 and 0.93 (0.63).
+// 2^19 / 2^20 / 2^21 / 2^22 / 2^23).  Bound by the copy, 57 GB/s of PCIe.
+// Factors in, an epoch, RMSE, factors out, in chunks of 2^25 and so (the copy
+// alone): 19.8 M samples, binary32, k = 128 8.2 and 5.0 ms (4.1); binary16,
+// k = 32 5.2 and 4.6 (4.1); pageable 16.2 and 9.8; 60 M 18.3 and 13.8 (12.5);
+// 5 M 2.35 and 1.78 (1.05); 3 M, k = 16 0.93 and 0.93 (0.63).  For a while after
+// device memory was freed (the first two epochs after an init, under 2 s after
+// 60 GB), copies queued one behind the other run at 30 GB/s; the epochs above
+// then take 7.9, 6.9, 9.6 and 24 ms, and narrow rows more than in one chunk.
 // Chunk i is copied into
 // device buffer i mod 3 on the library's copy stream while the caller's
 // stream runs the batch-Hogwild! kernel (one address space) over chunk i-1;
